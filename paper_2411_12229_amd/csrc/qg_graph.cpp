@@ -4,9 +4,10 @@
 // data of every vertex), searches every vector with Algorithm 1 (beam EF, EF
 // results) through the same search kernels as queries, turns the results and
 // the current neighbours into sorted candidate lists, and applies the NSG
-// pruning rule; every list is replaced at once.  Then the refinement
-// supplements edges up to R, random ids fill vertices with too few candidates,
-// and unreachable vertices are linked from their nearest reachable vertex.
+// pruning rule; every list is replaced at once.  In the last iteration the
+// refinement supplements edges up to R and random ids fill vertices with too
+// few candidates.  Then unreachable vertices are linked from their nearest
+// reachable vertex.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -14,6 +15,7 @@
 #include <cstdio>
 #include <cstring>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "qg.h"
@@ -99,15 +101,10 @@ extern "C" int qg_build_graph(const float* vectors, int64_t n, int32_t d, int32_
     std::fprintf(stderr, "[qg_build_graph] %.1fs %s %d: %lld\n", s, what, i, (long long)count);
     std::fflush(stderr);
   };
-  const int C = ef_build + r;  // candidate capacity: EF results and R old neighbours
   const int64_t chunk = std::min<int64_t>(n, 65536);
-  DevBuf G, cid, cd, ncand, kidx, nkept, sids, sdist;
+  DevBuf G, Gnew, sids, sdist;
   HIP_OR_FAIL(G.alloc(sizeof(int32_t) * (size_t)(n * r)), "hipMalloc graph");
-  HIP_OR_FAIL(cid.alloc(sizeof(int32_t) * (size_t)(n * C)), "hipMalloc candidates");
-  HIP_OR_FAIL(cd.alloc(sizeof(double) * (size_t)(n * C)), "hipMalloc candidate distances");
-  HIP_OR_FAIL(ncand.alloc(sizeof(int32_t) * (size_t)n), "hipMalloc candidate counts");
-  HIP_OR_FAIL(kidx.alloc(sizeof(int32_t) * (size_t)(n * r)), "hipMalloc kept indices");
-  HIP_OR_FAIL(nkept.alloc(sizeof(int32_t) * (size_t)n), "hipMalloc kept counts");
+  HIP_OR_FAIL(Gnew.alloc(sizeof(int32_t) * (size_t)(n * r)), "hipMalloc next graph");
   HIP_OR_FAIL(sids.alloc(sizeof(int32_t) * (size_t)(chunk * ef_build)), "hipMalloc search ids");
   HIP_OR_FAIL(sdist.alloc(sizeof(float) * (size_t)(chunk * ef_build)), "hipMalloc search distances");
   HIP_OR_FAIL(hipMemcpy(G.p, init_graph, sizeof(int32_t) * (size_t)(n * r), hipMemcpyDeviceToDevice), "copy graph");
@@ -121,30 +118,18 @@ extern "C" int qg_build_graph(const float* vectors, int64_t n, int32_t d, int32_
       rc = qg_search_ex(idx, vectors + q0 * d, nq, ef_build, ef_build, 0, sids.as<int32_t>(), sdist.as<float>(),
                         nullptr);
       if (rc == QG_OK) {
-        const hipError_t e = qgg::launch_candidates(vectors, d, sids.as<int32_t>(), ef_build, G.as<int32_t>(), r, q0,
-                                                    nq, C, cid.as<int32_t>(), cd.as<double>(), ncand.as<int32_t>(),
-                                                    nullptr);
-        if (e != hipSuccess) rc = hip_err(e, "candidates");
+        const hipError_t e = qgg::launch_prune(vectors, d, sids.as<int32_t>(), ef_build, G.as<int32_t>(), r, n, q0,
+                                               nq, refine && it + 1 == iters, fill, Gnew.as<int32_t>(), nullptr);
+        if (e != hipSuccess) rc = hip_err(e, "pruning");
       }
     }
     const hipError_t es = hipDeviceSynchronize();
     qg_free_index(idx);
     if (rc) return rc;
-    HIP_OR_FAIL(es, "search for candidates");
-    note("iteration, vertices searched", it, n);
-    HIP_OR_FAIL(qgg::launch_nsg(vectors, d, r, n, C, cid.as<int32_t>(), cd.as<double>(), ncand.as<int32_t>(),
-                                G.as<int32_t>(), kidx.as<int32_t>(), nkept.as<int32_t>(), nullptr),
-                "NSG pruning");
-    if (flags & QG_GRAPH_PROGRESS) {
-      HIP_OR_FAIL(hipDeviceSynchronize(), "NSG pruning");
-      note("iteration, lists pruned", it, n);
-    }
+    HIP_OR_FAIL(es, "search and pruning");
+    std::swap(G.p, Gnew.p);  // all lists are replaced at once
+    note("iteration, vertices searched and lists pruned", it, n);
   }
-  if (refine)
-    HIP_OR_FAIL(qgg::launch_refine(vectors, d, r, n, C, 1, cid.as<int32_t>(), ncand.as<int32_t>(),
-                                   kidx.as<int32_t>(), nkept.as<int32_t>(), fill, G.as<int32_t>(), nullptr),
-                "refinement");
-  HIP_OR_FAIL(hipDeviceSynchronize(), "graph construction");
   if (refine) note("refinement done", iters - 1, n);
 
   int64_t stats[4] = {0, 0, 0, 0};

@@ -8,7 +8,8 @@
 // multiply and add per term (compiled with -ffp-contract=off), of differences
 // of fp32 coordinates widened to fp64; cosines divide by the product of two
 // square roots.  One lane computes one such sum, so its order is the
-// sequential one.
+// sequential one.  Where an approximation with a known error already decides
+// a comparison, the sum is not computed (prune_kernel).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -24,8 +25,10 @@ __device__ __forceinline__ int lanes_below(uint64_t m) {
 __device__ __forceinline__ int first_lane(uint64_t m) { return __ffsll((unsigned long long)m) - 1; }
 
 // sum_t ((double)a[t] - (double)b[t])^2, t ascending
+template <int U>  // four-dimension steps unrolled (their loads in flight together)
 __device__ __forceinline__ double dist2_seq(const float* __restrict__ a, const float* __restrict__ b, int D) {
   double s = 0.0;
+#pragma unroll U
   for (int t = 0; t < D; t += 4) {
     const float4 x = *reinterpret_cast<const float4*>(a + t);
     const float4 y = *reinterpret_cast<const float4*>(b + t);
@@ -41,250 +44,477 @@ __device__ __forceinline__ double dist2_seq(const float* __restrict__ a, const f
   return s;
 }
 
-// (d, id) ascending
-__device__ __forceinline__ bool cand_greater(double da, int32_t ia, double db, int32_t ib) {
-  return da > db || (da == db && ia > ib);
+// ------------------------------------------------------------------ pruning
+
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+typedef float float16v __attribute__((ext_vector_type(16)));
+
+constexpr int kPruneWaves = 8;
+constexpr int kPruneThreads = 64 * kPruneWaves;
+// Bound on the error of a cosine the matrix cores compute from unit vectors
+// rounded to f16 (see prune_kernel): each element is off by at most 2^-11 of
+// itself, so the product sum by at most (2^-10 + 2^-22) sum |a||b| <= 2^-10 +
+// 2^-22 (Cauchy-Schwarz); f16 subnormals flushed to zero add below 2^-19
+// (elements are scaled by 2^12) and fp32 accumulation below D 2^-23 <= 2^-13
+// for D <= 1024.  Sum 1.11e-3.
+constexpr float kCosErr = 1.25e-3f;
+constexpr float kUnitScale = 4096.0f;                        // f16 elements hold 2^12 times the unit vector's
+constexpr float kDotScale = 1.0f / (kUnitScale * kUnitScale);
+
+// Dynamic LDS of prune_kernel (bytes).  stage: the f16 rows of one chunk of KC
+// dimensions, and before that the sort; occ: row w's bits over the 32-blocks
+// from its own on; per candidate: exact distance, t value, id, the two scaled
+// norms and the largest approximate cosine.
+struct PruneLds {
+  int stage, occ, cd, tv, id, rw, hv, cmax, queue, kept, total;
+};
+__host__ __device__ inline PruneLds prune_lds(int C, int R, int KC) {
+  const int nt = (C + 31) / 32, Cp = 32 * nt;
+  int P = 1;
+  while (P < C) P <<= 1;
+  PruneLds s{};
+  int o = 0;
+  const int st = 2 * KC * Cp, so = 12 * P;
+  s.stage = o;  o += ((st > so ? st : so) + 15) & ~15;
+  s.occ = o;    o += 4 * 32 * (nt * (nt + 1) / 2);
+  s.cd = o;     o += 8 * Cp;
+  s.tv = o;     o += 8 * Cp;
+  s.id = o;     o += 4 * Cp;
+  s.rw = o;     o += 4 * Cp;
+  s.hv = o;     o += 4 * Cp;
+  s.cmax = o;   o += 4 * Cp;
+  s.queue = o;  o += 4 * 128 * kPruneWaves;
+  s.kept = o;   o += 4 * R + 4 * 64 + 16;  // kept ids, kept bits, scalars
+  s.total = (o + 15) & ~15;
+  return s;
 }
 
-// Candidates of vertex u (Alg. 2, the search step of each iteration): the
-// search results for x_u that are not u, then u's current neighbours not among
-// them and not u; each with its exact squared distance to u; sorted by
-// (distance, id).  One wavefront per vertex of the chunk; P = the candidate
-// capacity rounded up to a power of two (LDS: P ids and P distances).
-__global__ __launch_bounds__(64) void candidates_kernel(const float* __restrict__ X, int D,
-                                                        const int32_t* __restrict__ sids, int EF,
-                                                        const int32_t* __restrict__ G, int R, int64_t u0, int C, int P,
-                                                        int32_t* __restrict__ cid, double* __restrict__ cd,
-                                                        int32_t* __restrict__ ncand) {
+__device__ __forceinline__ void wave_sync() { __builtin_amdgcn_wave_barrier(); }
+
+// Doubles as integers of the same order (cosines; no NaN is ever stored).
+__device__ __forceinline__ unsigned long long sortable64(double x) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(x);
+  return (u >> 63) ? ~u : (u | 0x8000000000000000ull);
+}
+__device__ __forceinline__ int sortable32(float x) {
+  const int u = __float_as_int(x);
+  return u < 0 ? (u ^ 0x7fffffff) : u;
+}
+__device__ __forceinline__ float unsortable32(int s) { return __int_as_float(s < 0 ? (s ^ 0x7fffffff) : s); }
+
+// sum_t (w_t - u_t)(v_t - u_t), t ascending, every term in fp64.
+__device__ __forceinline__ double dot_seq(const float* __restrict__ xw, const float* __restrict__ xv,
+                                          const float* __restrict__ xu, int D) {
+  double s = 0.0;
+#pragma unroll 2
+  for (int t = 0; t < D; t += 4) {
+    const float4 w4 = *reinterpret_cast<const float4*>(xw + t);
+    const float4 v4 = *reinterpret_cast<const float4*>(xv + t);
+    const float4 u4 = *reinterpret_cast<const float4*>(xu + t);
+    s = s + ((double)w4.x - (double)u4.x) * ((double)v4.x - (double)u4.x);
+    s = s + ((double)w4.y - (double)u4.y) * ((double)v4.y - (double)u4.y);
+    s = s + ((double)w4.z - (double)u4.z) * ((double)v4.z - (double)u4.z);
+    s = s + ((double)w4.w - (double)u4.w) * ((double)v4.w - (double)u4.w);
+  }
+  return s;
+}
+
+// One vertex u per workgroup of 8 wavefronts: candidate list, NSG rule and, on
+// the last iteration, refinement and random fill.
+//
+// Candidates (Alg. 2, the search step of each iteration): the search results
+// for x_u that are not u, then u's current neighbours not among them and not
+// u; each with its exact squared distance to u; sorted by (distance, id).
+//
+// NSG rule (Sec. 3.2.1): scan the sorted candidates and keep v unless an
+// already kept w is closer to v than u is, until R are kept.
+//
+// Refinement (Sec. 3.2.2).  For a vertex with fewer than R kept neighbours,
+// each pruned candidate v gets t_v = the largest cosine, at u, between v and a
+// candidate w closer to u (by (distance, id)); v survives an angle threshold
+// theta iff t_v <= cos(theta).  The largest threshold leaving R - nk survivors
+// has cos(theta*) = the (R - nk)-th smallest t_v (the limit of the paper's
+// binary search); survivors are added in distance order.  Then fill[u]
+// supplies neighbours while fewer than R are held (the paper's footnote:
+// random neighbours when candidates are too few).
+//
+// Both rules ask about every pair of candidates w < v: is |w - v| < |v - u|,
+// and is cos(w, v) the largest for v.  The pairs' cosines at u are products of
+// a matrix of unit vectors with its transpose, so the matrix cores compute
+// them all, from f16, with an error of at most kCosErr.  |w - v|^2 < |v - u|^2
+// iff cos > |w - u| / (2 |v - u|), so every pair further than the error from
+// that line is decided, and only a cosine within twice the error of its
+// column's largest can be that column's largest.  The pairs that are left
+// (about one in a hundred) are computed as the rules state them, in fp64, by
+// lanes in parallel; every decision and every t_v is therefore exactly that of
+// the fp64 rule.  What remains of the NSG scan is one AND of a bit row per
+// kept vertex.
+//
+// Computing every tested pair in fp64 by one lane each is what bound the
+// pruning before: 50,000 x 128 at 232 candidates took 123 ms for the
+// refinement, 4.4 ms per NSG pass and 2.9 ms for the candidate lists, and
+// takes 6.5 ms per iteration now, refinement included; 6,001 x 960 at 214
+// candidates 287, 8.6 and 1.5 ms, now 4.8 ms.  What bounds it now is latency:
+// the rows' loads and the one or two rounds of exact sums per vertex.
+// T: 32 x 32 tiles of cosines a wavefront holds in one pass over the
+// dimensions (16 registers each).
+struct PruneArgs {
+  const float* X;
+  int64_t N;
+  const int32_t* sids;  // [nu][EF] search results of vertices u0 ..
+  const int32_t* G;     // [N][R] the current graph
+  const int32_t* fill;
+  int32_t* Gout;  // [N][R] (not G)
+  int64_t u0;
+  int D, EF, R, C, KC, refine;
+};
+
+template <int T>
+__global__ __launch_bounds__(kPruneThreads, T <= 5 ? 4 : 2) void prune_kernel(PruneArgs a) {
   extern __shared__ __align__(16) uint8_t sm[];
-  double* ld = reinterpret_cast<double*>(sm);
-  int32_t* li = reinterpret_cast<int32_t*>(sm + 8 * (size_t)P);
-  const int lane = lane_id();
-  const int64_t u = u0 + blockIdx.x;
-  const int32_t* srow = sids + (int64_t)blockIdx.x * EF;
-  int n = 0;
-  for (int a0 = 0; a0 < EF; a0 += 64) {
-    const int a = a0 + lane;
-    const int32_t v = a < EF ? srow[a] : -1;
-    const bool ok = v >= 0 && v != (int32_t)u;
-    const uint64_t m = ballot(ok);
-    if (ok) li[n + lanes_below(m)] = v;
-    n += __popcll(m);
-  }
-  __syncthreads();
-  for (int j = 0; j < R; ++j) {
-    const int32_t v = G[u * R + j];
-    if (v < 0 || v == (int32_t)u) continue;
-    bool dup = false;
-    for (int i = lane; i < n; i += 64) dup |= li[i] == v;
-    if (ballot(dup)) continue;
-    if (lane == 0) li[n] = v;
-    ++n;
-    __syncthreads();
-  }
+  const int tid = threadIdx.x, lane = lane_id();
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int D = a.D, R = a.R, C = a.C, KC = a.KC;
+  const float* __restrict__ X = a.X;
+  const PruneLds L = prune_lds(C, R, KC);
+  _Float16* stage = reinterpret_cast<_Float16*>(sm + L.stage);
+  uint32_t* occ = reinterpret_cast<uint32_t*>(sm + L.occ);
+  double* cd = reinterpret_cast<double*>(sm + L.cd);
+  unsigned long long* tv = reinterpret_cast<unsigned long long*>(sm + L.tv);
+  int32_t* id = reinterpret_cast<int32_t*>(sm + L.id);
+  float* rw = reinterpret_cast<float*>(sm + L.rw);
+  float* hv = reinterpret_cast<float*>(sm + L.hv);
+  int32_t* cmax = reinterpret_cast<int32_t*>(sm + L.cmax);
+  uint32_t* queue = reinterpret_cast<uint32_t*>(sm + L.queue) + 128 * wave;
+  int32_t* kept = reinterpret_cast<int32_t*>(sm + L.kept);  // R ids
+  uint32_t* kbits = reinterpret_cast<uint32_t*>(kept + R);  // kept candidates, 32 a word (at most 34 words)
+  int32_t* scal = reinterpret_cast<int32_t*>(kbits + 64);   // [0] candidate count, [1] kept count
+  unsigned long long* cstar = reinterpret_cast<unsigned long long*>(sm + L.queue);  // once the queues are empty
+  const int64_t u = a.u0 + blockIdx.x;
   const float* xu = X + u * D;
-  for (int i = lane; i < P; i += 64) {
-    if (i < n) {
-      ld[i] = dist2_seq(xu, X + (int64_t)li[i] * D, D);
-    } else {
-      ld[i] = __builtin_inf();
-      li[i] = 0x7fffffff;
+
+  // ---- the candidates' ids
+  int P = 1;
+  while (P < C) P <<= 1;
+  unsigned long long* sk = reinterpret_cast<unsigned long long*>(sm + L.stage);  // P sort keys: distance bits
+  int32_t* si = reinterpret_cast<int32_t*>(sk + P);                               // P ids
+  if (wave == 0) {
+    const int32_t* srow = a.sids + (int64_t)blockIdx.x * a.EF;
+    int n = 0;
+    for (int e0 = 0; e0 < a.EF; e0 += 64) {
+      const int e = e0 + lane;
+      const int32_t v = e < a.EF ? srow[e] : -1;
+      const bool ok = v >= 0 && v != (int32_t)u;
+      const uint64_t m = ballot(ok);
+      if (ok) si[n + lanes_below(m)] = v;
+      n += __popcll(m);
     }
+    if (lane == 0) scal[0] = n;
   }
   __syncthreads();
-  for (int k = 2; k <= P; k <<= 1)
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int i = lane; i < P; i += 64) {
-        const int l = i ^ j;
-        if (l > i) {
-          const bool up = (i & k) == 0;
-          const double di = ld[i], dl = ld[l];
-          const int32_t ii = li[i], il = li[l];
-          if (cand_greater(di, ii, dl, il) == up) {
-            ld[i] = dl;
-            ld[l] = di;
-            li[i] = il;
-            li[l] = ii;
-          }
-        }
-      }
-      __syncthreads();
-    }
-  for (int i = lane; i < n; i += 64) {
-    cid[u * C + i] = li[i];
-    cd[u * C + i] = ld[i];
-  }
-  if (lane == 0) ncand[u] = n;
-}
-
-// NSG pruning rule (Sec. 3.2.1): scan the sorted candidates and keep v unless
-// an already kept w is closer to v than u is, until R are kept.  The 64
-// candidates of a chunk are tested against the kept set in parallel, then
-// resolved in order: the first undecided one is kept and tests the later ones.
-__global__ __launch_bounds__(64) void nsg_kernel(const float* __restrict__ X, int D, int R, int64_t N, int C,
-                                                 const int32_t* __restrict__ cid, const double* __restrict__ cd,
-                                                 const int32_t* __restrict__ ncand, int32_t* __restrict__ Gout,
-                                                 int32_t* __restrict__ kidx, int32_t* __restrict__ nkept) {
-  extern __shared__ __align__(16) uint8_t sm[];
-  int32_t* kept = reinterpret_cast<int32_t*>(sm);  // R ids
-  const int lane = lane_id();
-  const int64_t u = blockIdx.x;
-  if (u >= N) return;
-  const int n = ncand[u];
-  int nk = 0;
-  for (int base = 0; base < n && nk < R; base += 64) {
-    const int i = base + lane;
-    const bool active = i < n;
-    const int32_t c = active ? cid[u * C + i] : 0;
-    const double di = active ? cd[u * C + i] : 0.0;
-    const float* xc = X + (int64_t)c * D;
-    bool decided = !active;  // occluded, kept, or past the list
-    for (int a = 0; a < nk; ++a) {
-      const int32_t w = kept[a];
-      if (!decided) decided = dist2_seq(X + (int64_t)w * D, xc, D) < di;
-    }
-    for (;;) {
-      const uint64_t m = ballot(!decided);
-      if (!m || nk >= R) break;
-      const int f = first_lane(m);
-      const int32_t w = __builtin_amdgcn_readlane(c, f);
-      if (lane == 0) {
-        kept[nk] = w;
-        kidx[u * R + nk] = base + f;
-      }
-      ++nk;
-      if (lane == f) decided = true;
-      if (!decided) decided = dist2_seq(X + (int64_t)w * D, xc, D) < di;
-      __syncthreads();
-    }
-  }
-  for (int j = lane; j < R; j += 64) Gout[u * R + j] = j < nk ? kept[j] : -1;
-  if (lane == 0) nkept[u] = nk;
-}
-
-// Graph refinement (Sec. 3.2.2) and random fill.  For a vertex with fewer than
-// R kept neighbours, each pruned candidate v gets t_v = the largest cosine, at
-// u, between v and a candidate w closer to u (by (distance, id)); v survives an
-// angle threshold theta iff t_v <= cos(theta).  The largest threshold leaving
-// R - nk survivors has cos(theta*) = the (R - nk)-th smallest t_v (the limit of
-// the paper's binary search); survivors are added in distance order.  Then
-// fill[u] supplies neighbours while fewer than R are held (the paper's
-// footnote: random neighbours when candidates are too few).  LDS: P pruned
-// candidate indices, P t values, P sort slots.
-__global__ __launch_bounds__(64) void refine_kernel(const float* __restrict__ X, int D, int R, int64_t N, int C, int P,
-                                                    int do_refine, const int32_t* __restrict__ cid,
-                                                    const int32_t* __restrict__ ncand, const int32_t* __restrict__ kidx,
-                                                    const int32_t* __restrict__ nkept,
-                                                    const int32_t* __restrict__ fill, int32_t* __restrict__ G) {
-  extern __shared__ __align__(16) uint8_t sm[];
-  double* tv = reinterpret_cast<double*>(sm);
-  double* srt = tv + P;
-  int32_t* pr = reinterpret_cast<int32_t*>(srt + P);
-  int32_t* row = pr + P;  // R
-  const int lane = lane_id();
-  const int64_t u = blockIdx.x;
-  if (u >= N) return;
-  const int n = ncand[u];
-  int nk = nkept[u];
-  for (int j = lane; j < R; j += 64) row[j] = G[u * R + j];
-  __syncthreads();
-  const int need = R - nk;
-  if (do_refine && need > 0) {
-    // the pruned candidates, in distance order (every candidate was scanned: fewer than R were kept)
-    int np = 0;
-    for (int b = 0; b < n; b += 64) {
-      const int i = b + lane;
-      bool isk = false;
-      for (int a = 0; a < nk; ++a) isk |= kidx[u * R + a] == i;
-      const bool p = i < n && !isk;
-      const uint64_t m = ballot(p);
-      if (p) pr[np + lanes_below(m)] = i;
-      np += __popcll(m);
-    }
+  {
+    // a neighbour list holds no id twice, so each is compared with the results
+    // alone; the order of appending does not matter (the list is sorted next)
+    const int nres = scal[0];
     __syncthreads();
-    const float* xu = X + u * D;
-    for (int a = lane; a < np; a += 64) {
-      const int i = pr[a];
-      const float* xv = X + (int64_t)cid[u * C + i] * D;
-      double nv = 0.0;
-      for (int t = 0; t < D; ++t) {
-        const double du = (double)xv[t] - (double)xu[t];
-        nv = nv + du * du;
-      }
-      double best = -2.0;
-      for (int w = 0; w < i; ++w) {
-        const float* xw = X + (int64_t)cid[u * C + w] * D;
-        double nw = 0.0, dot = 0.0;
-        for (int t = 0; t < D; t += 4) {
-          const float4 w4 = *reinterpret_cast<const float4*>(xw + t);
-          const float4 v4 = *reinterpret_cast<const float4*>(xv + t);
-          const float4 u4 = *reinterpret_cast<const float4*>(xu + t);
-          double dw = (double)w4.x - (double)u4.x, dv = (double)v4.x - (double)u4.x;
-          nw = nw + dw * dw;
-          dot = dot + dw * dv;
-          dw = (double)w4.y - (double)u4.y;
-          dv = (double)v4.y - (double)u4.y;
-          nw = nw + dw * dw;
-          dot = dot + dw * dv;
-          dw = (double)w4.z - (double)u4.z;
-          dv = (double)v4.z - (double)u4.z;
-          nw = nw + dw * dw;
-          dot = dot + dw * dv;
-          dw = (double)w4.w - (double)u4.w;
-          dv = (double)v4.w - (double)u4.w;
-          nw = nw + dw * dw;
-          dot = dot + dw * dv;
-        }
-        const double cs = (nv > 0.0 && nw > 0.0) ? dot / (__builtin_sqrt(nv) * __builtin_sqrt(nw)) : 1.0;
-        if (cs > best) best = cs;
-      }
-      tv[a] = best;
-    }
-    __syncthreads();
-    if (np > 0) {
-      int Q = 1;
-      while (Q < np) Q <<= 1;
-      for (int a = lane; a < Q; a += 64) srt[a] = a < np ? tv[a] : __builtin_inf();
-      __syncthreads();
-      for (int k = 2; k <= Q; k <<= 1)
-        for (int j = k >> 1; j > 0; j >>= 1) {
-          for (int a = lane; a < Q; a += 64) {
-            const int l = a ^ j;
-            if (l > a) {
-              const bool up = (a & k) == 0;
-              const double x = srt[a], y = srt[l];
-              if ((x > y) == up) {
-                srt[a] = y;
-                srt[l] = x;
-              }
-            }
-          }
-          __syncthreads();
-        }
-      const double cstar = srt[(need <= np ? need : np) - 1];
-      for (int a = 0; a < np && nk < R; ++a)
-        if (tv[a] <= cstar) {
-          if (lane == 0) row[nk] = cid[u * C + pr[a]];
-          ++nk;
-        }
-      __syncthreads();
-    }
-  }
-  if (do_refine) {
-    // too few candidates: random neighbours
-    for (int f = 0; nk < R && f < R; ++f) {
-      const int32_t v = fill[u * R + f];
+    for (int j = wave; j < R; j += kPruneWaves) {
+      const int32_t v = a.G[u * R + j];
       if (v < 0 || v == (int32_t)u) continue;
       bool dup = false;
-      for (int a = lane; a < nk; a += 64) dup |= row[a] == v;
-      if (ballot(dup)) continue;
-      if (lane == 0) row[nk] = v;
-      ++nk;
-      __syncthreads();
+      for (int i = lane; i < nres; i += 64) dup |= si[i] == v;
+      if (!ballot(dup) && lane == 0) si[atomicAdd(&scal[0], 1)] = v;
     }
   }
   __syncthreads();
-  for (int j = lane; j < R; j += 64) G[u * R + j] = row[j];
+  const int n = __builtin_amdgcn_readfirstlane(scal[0]);
+  for (int i = tid; i < P; i += kPruneThreads) {
+    unsigned long long k = ~0ull;  // padding sorts last
+    if (i < n)
+      k = (unsigned long long)__double_as_longlong(dist2_seq<8>(xu, X + (int64_t)si[i] * D, D));
+    else
+      si[i] = 0x7fffffff;
+    sk[i] = k;  // a sum of squares: its bits order as the value does
+  }
+  __syncthreads();
+  // bitonic sort; with a distance of at most 64 between partners a wavefront's
+  // 128 elements are its own, so only the wider steps need the barrier
+  for (int k = 2; k <= P; k <<= 1)
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      for (int t = tid; t < P / 2; t += kPruneThreads) {
+        const int i = ((t & ~(j - 1)) << 1) | (t & (j - 1)), l = i | j;
+        const bool up = (i & k) == 0;
+        const unsigned long long di = sk[i], dl = sk[l];
+        const int32_t ii = si[i], il = si[l];
+        if ((di > dl || (di == dl && ii > il)) == up) {
+          sk[i] = dl;
+          sk[l] = di;
+          si[i] = il;
+          si[l] = ii;
+        }
+      }
+      if (j > 64 || (j == 1 && k >= 128))
+        __syncthreads();
+      else
+        wave_sync();
+    }
+  __syncthreads();
+  const int nt = (n + 31) / 32, nc = 32 * nt;
+  const double smax = n > 0 ? __builtin_sqrt(__longlong_as_double((long long)sk[n - 1])) : 0.0;
+  const double ismax = smax > 0.0 ? 1.0 / smax : 0.0;
+  for (int i = tid; i < nc; i += kPruneThreads) {
+    const bool live = i < n;
+    const double d = live ? __longlong_as_double((long long)sk[i]) : 0.0;
+    const double r = __builtin_sqrt(d) * ismax;
+    cd[i] = d;
+    id[i] = live ? si[i] : 0;
+    rw[i] = (float)r;
+    hv[i] = live ? 0.5f / (float)r : 0.0f;
+    cmax[i] = sortable32(-2.0f);
+    tv[i] = sortable64(-2.0);
+  }
+
+  // ---- every pair's cosine, and the pairs it does not decide
+  // tile p of the triangle: columns (v) block J, rows (w) block I <= J
+  auto occ_row = [&](int w) {  // word of block w / 32 in row w
+    const int I = w >> 5;
+    return 32 * (I * nt - I * (I - 1) / 2) + (w & 31) * (nt - I);
+  };
+  auto eval = [&](int which, uint32_t e) {
+    const int w = (int)(e >> 16), v = (int)(e & 0xffffu);
+    const float* xw = X + (int64_t)id[w] * D;
+    const float* xv = X + (int64_t)id[v] * D;
+    if (which == 0) {
+      if (dist2_seq<4>(xw, xv, D) < cd[v]) atomicOr(&occ[occ_row(w) + (v >> 5) - (w >> 5)], 1u << (v & 31));
+    } else {
+      const double nw = cd[w], nv = cd[v];
+      const double cs = (nv > 0.0 && nw > 0.0) ? dot_seq(xw, xv, xu, D) / (__builtin_sqrt(nv) * __builtin_sqrt(nw))
+                                               : 1.0;
+      if (cs > -2.0) atomicMax(&tv[v], sortable64(cs));
+    }
+  };
+  const int half = lane >> 5;
+  // Computes the pairs marked in mask (bit i of tile t: register i of its
+  // cosines) exactly, 64 at a time: marked pairs are compacted into the
+  // wavefront's queue, one bit per lane and step.
+  auto drain = [&](int which, uint32_t (&mask)[(T + 1) / 2], const int (&tile)[T]) {
+    int qn = 0;
+    bool more = true;
+    while (more) {
+      more = false;
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        const int I = tile[t] & 255, J = tile[t] >> 8;
+        for (;;) {
+          const uint32_t mine = (mask[t >> 1] >> (16 * (t & 1))) & 0xffffu;
+          const uint64_t m = ballot(mine != 0);
+          if (!m) break;
+          if (qn >= 64) {
+            more = true;
+            break;
+          }
+          if (mine) {
+            const int i = __builtin_ctz(mine);
+            const int w = 32 * I + 8 * (i >> 2) + 4 * half + (i & 3);
+            queue[qn + lanes_below(m)] = (uint32_t)w << 16 | (uint32_t)(32 * J + (lane & 31));
+            mask[t >> 1] &= ~(1u << (i + 16 * (t & 1)));
+          }
+          qn += __popcll(m);
+        }
+      }
+      wave_sync();
+      if (lane < qn) eval(which, queue[lane]);
+      qn = qn > 64 ? qn - 64 : 0;
+      const uint32_t rest = lane < qn ? queue[64 + lane] : 0u;
+      wave_sync();
+      if (lane < qn) queue[lane] = rest;
+      wave_sync();
+      more = more || qn > 0;
+    }
+  };
+  const int npairs = nt * (nt + 1) / 2;
+  const int passes = (npairs + T * kPruneWaves - 1) / (T * kPruneWaves);
+  const int per = passes ? (npairs + passes * kPruneWaves - 1) / (passes * kPruneWaves) : 0;  // tiles a wavefront holds
+  const int rowsh = KC == 32 ? 3 : 2;  // log2 of the lanes staging one row (four dimensions each)
+  for (int pass = 0; pass < passes; ++pass) {
+    const int p0 = (pass * kPruneWaves + wave) * per;
+    const int mine = p0 >= npairs ? 0 : (npairs - p0 < per ? npairs - p0 : per);
+    int tile[T];  // I | J << 8
+    {
+      int J = 0;
+      while ((J + 1) * (J + 2) / 2 <= p0) ++J;
+      int I = p0 - J * (J + 1) / 2;
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        tile[t] = __builtin_amdgcn_readfirstlane(I | (J << 8));
+        if (++I > J) {
+          ++J;
+          I = 0;
+        }
+      }
+    }
+    float16v acc[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[t][i] = 0.0f;
+    for (int k0 = 0; k0 < D; k0 += KC) {
+      __syncthreads();
+      {
+        // row r's KC dimensions, 16-byte slots swizzled by the row so that the
+        // operand reads of eight consecutive rows fall in different banks
+        const int c = (tid & ((1 << rowsh) - 1)) * 4;
+        const float4 u4 = *reinterpret_cast<const float4*>(xu + k0 + c);
+        for (int r = tid >> rowsh; r < nc; r += kPruneThreads >> rowsh) {
+          const float4 x4 = *reinterpret_cast<const float4*>(X + (int64_t)id[r] * D + k0 + c);
+          const float f = hv[r] * (2.0f * kUnitScale);  // 2^12 |max| / |r|; 0 for padding
+          half4 h;
+          h.x = (_Float16)((float)(((double)x4.x - (double)u4.x) * ismax) * f);
+          h.y = (_Float16)((float)(((double)x4.y - (double)u4.y) * ismax) * f);
+          h.z = (_Float16)((float)(((double)x4.z - (double)u4.z) * ismax) * f);
+          h.w = (_Float16)((float)(((double)x4.w - (double)u4.w) * ismax) * f);
+          const int slot = KC == 32 ? (c >> 3) ^ ((r >> 1) & 3) : (c >> 3) ^ ((r >> 2) & 1);
+          *reinterpret_cast<half4*>(stage + r * KC + slot * 8 + (c & 4)) = h;
+        }
+      }
+      __syncthreads();
+      for (int ks = 0; ks < KC; ks += 16) {
+        const int s = (ks >> 3) + (lane >> 5), r = lane & 31;
+        const int slot = KC == 32 ? s ^ ((r >> 1) & 3) : s ^ ((r >> 2) & 1);
+        const _Float16* base = stage + r * KC + slot * 8;
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+          if (t < mine) {
+            const half8 A = *reinterpret_cast<const half8*>(base + (tile[t] & 255) * 32 * KC);
+            const half8 B = *reinterpret_cast<const half8*>(base + (tile[t] >> 8) * 32 * KC);
+            acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(A, B, acc[t], 0, 0, 0);
+          }
+      }
+    }
+    // lane l holds column v = 32 J + l % 32, rows w = 32 I + 8 (i / 4) + 4 (l / 32) + i % 4
+    uint32_t mask[(T + 1) / 2];
+#pragma unroll
+    for (int t = 0; t < (T + 1) / 2; ++t) mask[t] = 0;
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+      if (t < mine) {
+        const int I = tile[t] & 255, J = tile[t] >> 8, v = 32 * J + (lane & 31);
+        const float h = hv[v];
+        const int w0 = 32 * I + 4 * half, below = (v < n ? v : 0) - w0;  // rows w0 + o with o < below are pairs
+        float cm = -2.0f;
+        uint32_t open = 0;  // pairs the approximation leaves open
+        uint32_t* ow = occ + occ_row(w0) + J - I;  // word of row w0 + o: o rows of nt - I words on
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int o = 8 * (i >> 2) + (i & 3), w = w0 + o;
+          const bool pair = o < below;
+          const float cs = acc[t][i] * kDotScale, thr = rw[w] * h;
+          const bool can = thr >= 1e-6f;  // else |w - u| is lost beside |v - u|; false for a zero or huge norm (NaN)
+          const bool yes = can && cs > thr + kCosErr, no = can && cs < thr - kCosErr;
+          const uint64_t ym = ballot(pair && yes);
+          if ((lane & 31) == 0) ow[o * (nt - I)] = half ? (uint32_t)(ym >> 32) : (uint32_t)ym;
+          open |= pair && !yes && !no ? 1u << i : 0u;
+          cm = pair && can ? fmaxf(cm, cs) : cm;
+          asm volatile("" : "+v"(open), "+v"(cm));  // row by row: the rows' conditions would fill the scalar registers
+        }
+        mask[t >> 1] |= open << (16 * (t & 1));
+        if (a.refine && cm > -2.0f) atomicMax(&cmax[v], sortable32(cm));
+      }
+    drain(0, mask, tile);
+    if (a.refine) {
+      __syncthreads();  // every wavefront's column maxima of this pass
+#pragma unroll
+      for (int t = 0; t < T; ++t)
+        if (t < mine) {
+          const int I = tile[t] & 255, J = tile[t] >> 8, v = 32 * J + (lane & 31);
+          const float h = hv[v], lim = unsortable32(cmax[v]) - 2.0f * kCosErr;
+          const int w0 = 32 * I + 4 * half, below = (v < n ? v : 0) - w0;
+          uint32_t open = 0;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            const int o = 8 * (i >> 2) + (i & 3);
+            const bool out = rw[w0 + o] * h >= 1e-6f && acc[t][i] * kDotScale < lim;
+            open |= o < below && !out ? 1u << i : 0u;
+            asm volatile("" : "+v"(open));
+          }
+          mask[t >> 1] |= open << (16 * (t & 1));
+        }
+      drain(1, mask, tile);
+    }
+  }
+  __syncthreads();
+
+  // ---- the NSG scan: wavefront 0, lane l holds the undecided candidates 32 l ..
+  if (wave == 0) {
+    uint32_t alive = 0, kb = 0;
+    if (lane < nt) alive = n - 32 * lane >= 32 ? ~0u : (1u << (n - 32 * lane)) - 1u;
+    int nk = 0;
+    while (nk < R) {
+      const uint64_t m = ballot(alive != 0);
+      if (!m) break;
+      const int J = first_lane(m);
+      const int b = __builtin_ctz((uint32_t)__builtin_amdgcn_readlane((int)alive, J));
+      const int f = 32 * J + b;
+      if (lane == 0) kept[nk] = id[f];
+      ++nk;
+      if (lane >= J && lane < nt) alive &= ~occ[occ_row(f) + lane - J];
+      if (lane == J) {
+        alive &= ~(1u << b);
+        kb |= 1u << b;
+      }
+    }
+    if (lane < nt) kbits[lane] = kb;
+    if (lane == 0) scal[1] = nk;
+  }
+  __syncthreads();
+  int nk = __builtin_amdgcn_readfirstlane(scal[1]);
+  if (a.refine && nk < R) {
+    // ---- refinement: the threshold is the need-th smallest t of the pruned
+    const int np = n - nk, need = R - nk < np ? R - nk : np;
+    for (int i = tid; i < n; i += kPruneThreads)
+      if ((kbits[i >> 5] >> (i & 31)) & 1) tv[i] = ~0ull;  // kept: counts above every pruned one
+    __syncthreads();
+    for (int i = tid; i < n; i += kPruneThreads) {
+      const unsigned long long x = tv[i];
+      if (x == ~0ull) continue;
+      int lt = 0, le = 0;
+#pragma unroll 4
+      for (int j = 0; j < n; ++j) {
+        const unsigned long long y = tv[j];
+        lt += y < x;
+        le += y <= x;
+      }
+      if (lt < need && need <= le) *cstar = x;  // the same value from every lane that finds it
+    }
+    __syncthreads();
+    if (wave == 0) {
+      const unsigned long long cut = np > 0 ? *cstar : 0ull;
+      for (int b = 0; b < n && nk < R; b += 64) {
+        const int i = b + lane;
+        const bool ok = i < n && tv[i] <= cut;
+        const uint64_t m = ballot(ok);
+        const int pos = nk + lanes_below(m);
+        if (ok && pos < R) kept[pos] = id[i];
+        nk = nk + __popcll(m) < R ? nk + __popcll(m) : R;
+      }
+      wave_sync();
+      // too few candidates: random neighbours
+      for (int f = 0; nk < R && f < R; ++f) {
+        const int32_t v = a.fill[u * R + f];
+        if (v < 0 || v == (int32_t)u) continue;
+        bool dup = false;
+        for (int k = lane; k < nk; k += 64) dup |= kept[k] == v;
+        if (ballot(dup)) continue;
+        if (lane == 0) kept[nk] = v;
+        ++nk;
+        wave_sync();
+      }
+    }
+  }
+  if (wave == 0) {
+    wave_sync();
+    for (int j = lane; j < R; j += 64) a.Gout[u * R + j] = j < nk ? kept[j] : -1;
+  }
 }
 
 // Repair helper: rows of X listed in ids, gathered into out[n][D].
@@ -305,49 +535,31 @@ __global__ __launch_bounds__(256) void rows_dist_kernel(const float* __restrict_
   if (i >= nw * R) return;
   const int64_t w = ws[i / R];
   const int32_t v = G[w * R + i % R];
-  out[i] = v >= 0 ? dist2_seq(X + w * D, X + (int64_t)v * D, D) : __builtin_inf();
+  out[i] = v >= 0 ? dist2_seq<8>(X + w * D, X + (int64_t)v * D, D) : __builtin_inf();
 }
 
-int pow2_at_least(int x) {
-  int p = 1;
-  while (p < x) p <<= 1;
-  return p;
-}
-
-hipError_t launch_candidates(const float* X, int D, const int32_t* sids, int EF, const int32_t* G, int R, int64_t u0,
-                             int64_t nu, int C, int32_t* cid, double* cd, int32_t* ncand, hipStream_t st) {
-  const int P = pow2_at_least(C);
-  const size_t lds = 12 * (size_t)P;
-  if (lds > 64 * 1024) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(candidates_kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(candidates_kernel, dim3((unsigned)nu), dim3(64), lds, st, X, D, sids, EF, G, R, u0, C, P, cid,
-                     cd, ncand);
-  return hipGetLastError();
-}
-
-hipError_t launch_nsg(const float* X, int D, int R, int64_t N, int C, const int32_t* cid, const double* cd,
-                      const int32_t* ncand, int32_t* Gout, int32_t* kidx, int32_t* nkept, hipStream_t st) {
-  hipLaunchKernelGGL(nsg_kernel, dim3((unsigned)N), dim3(64), 4 * (size_t)R, st, X, D, R, N, C, cid, cd, ncand, Gout,
-                     kidx, nkept);
-  return hipGetLastError();
-}
-
-hipError_t launch_refine(const float* X, int D, int R, int64_t N, int C, int do_refine, const int32_t* cid,
-                         const int32_t* ncand, const int32_t* kidx, const int32_t* nkept, const int32_t* fill,
-                         int32_t* G, hipStream_t st) {
-  const int P = pow2_at_least(C);
-  const size_t lds = 20 * (size_t)P + 4 * (size_t)R;
-  if (lds > 64 * 1024) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(refine_kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(refine_kernel, dim3((unsigned)N), dim3(64), lds, st, X, D, R, N, C, P, do_refine, cid, ncand, kidx,
-                     nkept, fill, G);
-  return hipGetLastError();
+hipError_t launch_prune(const float* X, int D, const int32_t* sids, int EF, const int32_t* G, int R, int64_t N,
+                        int64_t u0, int64_t nu, int refine, const int32_t* fill, int32_t* Gout, hipStream_t st) {
+  if (nu <= 0) return hipSuccess;
+  const int C = EF + R;  // EF results and R old neighbours
+  if (D % 32 || D > 1024 || R > 64 || C > 32 * 34) return hipErrorInvalidValue;
+  // chunks of 32 dimensions, or 16 where the lists are so long that the LDS asks for it
+  const int KC = prune_lds(C, R, 32).total <= 160 * 1024 ? 32 : 16;
+  const size_t lds = (size_t)prune_lds(C, R, KC).total;
+  const PruneArgs a{X, N, sids, G, fill, Gout, u0, D, EF, R, C, KC, refine};
+  // lists of up to 256 candidates are 36 tiles, 5 a wavefront: few enough
+  // registers for two workgroups on a compute unit; longer lists hold 10 a
+  // wavefront and go over the dimensions again for the tiles beyond 80
+  auto go = [&](auto kern) {
+    if (lds > 64 * 1024) {
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)nu), dim3(kPruneThreads), lds, st, a);
+    return hipGetLastError();
+  };
+  return C <= 256 ? go(prune_kernel<5>) : go(prune_kernel<10>);
 }
 
 hipError_t launch_gather(const float* X, int D, const int32_t* ids, int64_t n, float* out, hipStream_t st) {
