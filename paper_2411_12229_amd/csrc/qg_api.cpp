@@ -272,24 +272,6 @@ int qg_build_index(const float* vectors, int64_t n, int32_t d, const int32_t* gr
   HIP_TRY(hipGetDeviceCount(&ndev), "hipGetDeviceCount");
   if (device < 0 || device >= ndev) return fail(QG_EINVAL, "bad device");
   DeviceGuard g(device);
-  {  // every neighbour id becomes a block address in the kernels: check them all here
-    std::vector<int32_t> h;
-    try {
-      h.resize((size_t)(n * r));
-    } catch (...) {
-      return fail(QG_ENOMEM, "host buffer");
-    }
-    HIP_TRY(hipMemcpy(h.data(), graph, sizeof(int32_t) * h.size(), hipMemcpyDeviceToHost), "copy graph");
-    for (int32_t v : h)
-      if (v < -1 || v >= n) return fail(QG_EINVAL, "graph id out of range");
-    bool rep = false;
-    try {
-      rep = has_repeated_id(n, r, [&](int64_t u, int j) { return h[(size_t)(u * r + j)]; });
-    } catch (...) {
-      return fail(QG_ENOMEM, "host buffer");
-    }
-    if (rep) return fail(QG_EINVAL, "a neighbour list repeats an id");
-  }
   qg_index* idx = new qg_index;
   idx->device = device;
   idx->N = n;
@@ -308,14 +290,23 @@ int qg_build_index(const float* vectors, int64_t n, int32_t d, const int32_t* gr
     return hip_fail(e, "hipMalloc rotated vectors");
   }
   e = hipMemcpy(idx->rot, rotation, sizeof(float) * d * d, hipMemcpyDeviceToDevice);
-  if (e == hipSuccess) e = hipMemset(idx->blocks, 0, (size_t)(n * idx->block_bytes));
+  // every neighbour id becomes a block address in the kernels: the encoder
+  // checks them all (the last counter, cleared above, is its flag; searches
+  // clear the counters again before they use them)
+  int bad = 0;
+  int* const flag = idx->counters + kCounters - 1;
   if (e == hipSuccess) e = qgk::launch_rotate(vectors, n, d, idx->rot, tmp, nullptr, 0, nullptr);
-  if (e == hipSuccess) e = qgk::launch_encode(vectors, tmp, n, d, graph, r, idx->blocks, idx->block_bytes, nullptr);
-  if (e == hipSuccess) e = hipDeviceSynchronize();
+  if (e == hipSuccess)
+    e = qgk::launch_encode(vectors, tmp, n, d, graph, r, idx->blocks, idx->block_bytes, flag, nullptr);
+  if (e == hipSuccess) e = hipMemcpy(&bad, flag, sizeof bad, hipMemcpyDeviceToHost);  // waits for the encoder
   (void)hipFree(tmp);
   if (e != hipSuccess) {
     release(idx);
     return hip_fail(e, "encode");
+  }
+  if (bad) {
+    release(idx);
+    return fail(QG_EINVAL, bad & 1 ? "graph id out of range" : "a neighbour list repeats an id");
   }
   *out = idx;
   return QG_OK;

@@ -60,8 +60,11 @@ hipError_t noalloc_scratch(int device, uint8_t** out);
 bool shape_supported(int D, int R);
 hipError_t launch_rotate(const float* in, int64_t n, int D, const float* M, float* out, int* zero, int nzero,
                          hipStream_t st);
+// Encodes every block; *flag (device, cleared by the caller) receives bit 0 for
+// an id outside [-1, N), bit 1 for an id that a list repeats (the blocks are
+// then not to be used).
 hipError_t launch_encode(const float* X, const float* ROT, int64_t N, int D, const int32_t* G, int R,
-                         uint8_t* blocks, int64_t B, hipStream_t st);
+                         uint8_t* blocks, int64_t B, int* flag, hipStream_t st);
 // ls_mode: 0 plain search, 1 learned stop (MLP staged in LDS, mlp_lds_bytes()
 // after the wavefront areas), 2 learned stop with trace (MLP read from global),
 // 3 per-query k and ef (k_q, ef_q set), 4 per-query k and ef with the learned

@@ -290,10 +290,49 @@ __global__ __launch_bounds__(64) void rotate_kernel(const float* __restrict__ in
 
 // ------------------------------------------------------------------ encode
 
-__device__ __forceinline__ double butterfly_d(double p) {
-#pragma unroll
-  for (int s = 32; s >= 1; s >>= 1) p = p + __shfl_xor(p, s, 64);
-  return p;
+// Data movement on doubles: the swap of the two wavefront halves (S = 32) or
+// of odd and even rows of 16 lanes (S = 16) between two values, and the DPP
+// moves of row_ror and xor_lane.
+template <int S>
+__device__ __forceinline__ void swap_d(double& a, double& b) {
+  const uint64_t x = (uint64_t)__double_as_longlong(a), y = (uint64_t)__double_as_longlong(b);
+  if constexpr (S == 32) {
+    const auto l = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+    a = __longlong_as_double((long long)((uint64_t)h[0] << 32 | l[0]));
+    b = __longlong_as_double((long long)((uint64_t)h[1] << 32 | l[1]));
+  } else {
+    const auto l = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+    a = __longlong_as_double((long long)((uint64_t)h[0] << 32 | l[0]));
+    b = __longlong_as_double((long long)((uint64_t)h[1] << 32 | l[1]));
+  }
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double x) {
+  const uint64_t u = (uint64_t)__double_as_longlong(x);
+  const uint32_t l = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, CTRL, 0xF, 0xF, false);
+  const uint32_t h = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), CTRL, 0xF, 0xF, false);
+  return __longlong_as_double((long long)((uint64_t)h << 32 | l));
+}
+
+// Four butterfly sums p[l] + p[l ^ s], s = 32 ... 1, at once: every swap hands
+// each half (row) the partner values of one of two sums, so one addition does
+// the stage for both, and every addition is of the pair its butterfly names.
+// Row r of 16 lanes ends with the total of value r (0, 2, 1, 3 for rows 0 ..
+// 3).  21 instructions in place of four butterflies' 72, and none through LDS.
+__device__ __forceinline__ double butterfly4_d(double p0, double p1, double p2, double p3) {
+  swap_d<32>(p0, p1);
+  double x = p0 + p1;  // halves: p0, p1
+  swap_d<32>(p2, p3);
+  double y = p2 + p3;  // halves: p2, p3
+  swap_d<16>(x, y);
+  double z = x + y;           // rows: p0, p2, p1, p3
+  z = z + dpp_d<0x128>(z);    // row_ror:8 (lane ^ 8)
+  z = z + dpp_d<0x124>(z);    // row_ror:4 (as lane ^ 4: lanes l and l ^ 8 hold the same bits)
+  z = z + dpp_d<0x4E>(z);     // lane ^ 2
+  z = z + dpp_d<0xB1>(z);     // lane ^ 1
+  return z;
 }
 
 // One wavefront per holder vertex c.  For every edge c -> o (Sec. 3.1.1,
@@ -301,67 +340,114 @@ __device__ __forceinline__ double butterfly_d(double p) {
 // |r|^2, sum |y_i| and xc = sum (2b_i - 1) rot(c)_i with dim i in lane i mod
 // 64 and a butterfly; f_rescale = -2|r|^2 / sum|y|, f_add = |r|^2 - f_rescale*xc
 // (Eq. normalization with Eq. 3.1; degenerate edge: f_rescale = 0,
-// f_add = |r|^2).  The block buffer must be zeroed beforehand.
+// f_add = |r|^2).  Writes every byte of the block.
+//
+// Four edges at a time: their rows' loads are in flight together, their sums
+// share the butterfly stages, and each row of 16 lanes finishes one edge.  An
+// empty slot runs as the edge c -> c, whose codes and factors are zero.
+// Bound by the gather of two rows per edge through L2 and the last-level cache
+// and, at D = 128, as much by issue: 100,000 x 128, R = 32 gathers 3.3 GB in
+// 0.475 ms (1.29 ms with one edge at a time and its butterflies through LDS);
+// 6,001 x 960, R = 64 gathers 2.95 GB in 0.354 ms (0.77 ms).  For the wide
+// shapes the unrolled loads matter more than residency: 24 loads in flight at
+// half the registers took 0.475 ms.
+//
+// The graph is checked on the way: *flag receives 1 for an id outside [-1, N)
+// (not followed: it runs as an empty slot) and 2 for an id that a list repeats.
+template <int D>
 __global__ __launch_bounds__(256) void encode_kernel(const float* __restrict__ X, const float* __restrict__ ROT,
-                                                     int64_t N, int D, const int32_t* __restrict__ G, int R,
-                                                     uint8_t* __restrict__ blocks, int64_t B) {
+                                                     int64_t N, const int32_t* __restrict__ G, int R,
+                                                     uint8_t* __restrict__ blocks, int64_t B, int* flag) {
+  constexpr int DPL = (D + 63) / 64;
+  constexpr bool kRagged = D % 64 != 0;  // the last chunk holds 32 dims (D is a multiple of 32)
+  static_assert(D % 32 == 0 && 4 * DPL <= 64, "one lane per code word of four edges");
   const int lane = lane_id();
   const int64_t c = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   if (c >= N) return;
-  const int DPL = (D + 63) >> 6;
   uint8_t* blk = blocks + c * B;
-  const float* xc = X + c * D;
-  const float* rc = ROT + c * D;
-  for (int i = lane; i < D; i += 64) reinterpret_cast<float*>(blk)[i] = xc[i];
+  const float* xrow = X + c * D;
+  const float* rrow = ROT + c * D;
+  const bool tail = !kRagged || lane < 32;  // lane has a dim in the last chunk
+  float xc[DPL], rc[DPL];
+#pragma unroll
+  for (int t = 0; t < DPL; ++t) {
+    const bool in = t + 1 < DPL || tail;
+    xc[t] = in ? xrow[lane + 64 * t] : 0.0f;
+    rc[t] = in ? rrow[lane + 64 * t] : 0.0f;
+    if (in) reinterpret_cast<float*>(blk)[lane + 64 * t] = xc[t];
+  }
+  for (int64_t o = qgl::off_nbr(D, R) + 4 * R + 4 * lane; o < B; o += 256) *reinterpret_cast<uint32_t*>(blk + o) = 0u;
   uint8_t* codes = blk + qgl::off_codes(D);
   float* fadd = reinterpret_cast<float*>(blk + qgl::off_fadd(D, R));
   float* fres = reinterpret_cast<float*>(blk + qgl::off_fres(D, R));
   int32_t* nbr = reinterpret_cast<int32_t*>(blk + qgl::off_nbr(D, R));
-  for (int j = 0; j < R; ++j) {
-    const int32_t o = G[c * R + j];
-    if (o < 0) {
-      if (lane == 0) {
-        fadd[j] = 0.0f;
-        fres[j] = 0.0f;
-        nbr[j] = -1;
-      }
-      continue;
+  const int32_t own = lane < R ? G[c * R + lane] : -1;  // lane j: neighbour j (R <= 64)
+  const bool bad = own < -1 || (int64_t)own >= N;
+  bool rep = false;
+  if (lane < R) nbr[lane] = bad ? -1 : own;
+  // neighbours are visited by four; R is a multiple of 4
+  for (int j = 0; j < R; j += 4) {
+    const float* xo[4];
+    const float* ro[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int32_t o = __builtin_amdgcn_readlane(own, j + e);
+      rep |= lane > j + e && own == o && o >= 0;
+      const int64_t v = o < 0 || (int64_t)o >= N ? c : (int64_t)o;
+      xo[e] = X + v * D;
+      ro[e] = ROT + v * D;
     }
-    const float* xo = X + (int64_t)o * D;
-    const float* ro = ROT + (int64_t)o * D;
-    double pr = 0.0, pa = 0.0, px = 0.0;
-    uint8_t* code = codes + (int64_t)j * (D / 8);
+    double pr[4] = {0.0, 0.0, 0.0, 0.0}, pa[4] = {0.0, 0.0, 0.0, 0.0}, px[4] = {0.0, 0.0, 0.0, 0.0};
+    uint32_t wlo = 0, whi = 0;  // lane e DPL + t: the code bits of edge e, dims 64 t ..
+#pragma unroll
     for (int t = 0; t < DPL; ++t) {
-      const int i = lane + 64 * t;
-      bool bit = false;
-      if (i < D) {
-        double d = (double)xo[i] - (double)xc[i];
-        pr = __builtin_fma(d, d, pr);
-        float y = ro[i] - rc[i];
-        bit = y > 0.0f;
-        pa = pa + __builtin_fabs((double)y);
-        px = bit ? px + (double)rc[i] : px - (double)rc[i];
+      const bool in = t + 1 < DPL || tail;
+      const int i = in ? lane + 64 * t : 0;
+      float xv[4], rv[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        xv[e] = xo[e][i];
+        rv[e] = ro[e][i];
       }
-      uint64_t m = ballot(bit);
-      const int nbytes = (D - 64 * t) >= 64 ? 8 : (D - 64 * t) / 8;
-      if (lane < nbytes) code[8 * t + lane] = (uint8_t)(m >> (8 * lane));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float y = rv[e] - rc[t];
+        const bool bit = in && y > 0.0f;
+        if (in) {
+          const double d = (double)xv[e] - (double)xc[t];
+          pr[e] = __builtin_fma(d, d, pr[e]);
+          pa[e] = pa[e] + __builtin_fabs((double)y);
+          px[e] = px[e] + (double)(bit ? rc[t] : -rc[t]);
+        }
+        const uint64_t m = ballot(bit);
+        const bool mine = lane == e * DPL + t;
+        wlo = mine ? (uint32_t)m : wlo;
+        whi = mine ? (uint32_t)(m >> 32) : whi;
+      }
     }
-    pr = butterfly_d(pr);
-    pa = butterfly_d(pa);
-    px = butterfly_d(px);
-    if (lane == 0) {
-      if (pa == 0.0) {
-        fres[j] = 0.0f;
-        fadd[j] = (float)pr;
-      } else {
-        double fr = (-2.0 * pr) / pa;
-        double fa = pr - fr * px;
-        fres[j] = (float)fr;
-        fadd[j] = (float)fa;
+    if (lane < 4 * DPL) {
+      const int e = lane / DPL, t = lane - e * DPL;
+      uint32_t* w = reinterpret_cast<uint32_t*>(codes + (int64_t)(j + e) * (D / 8) + 8 * t);
+      w[0] = wlo;
+      if (!kRagged || t + 1 < DPL) w[1] = whi;
+    }
+    const double r2 = butterfly4_d(pr[0], pr[1], pr[2], pr[3]);
+    const double sa = butterfly4_d(pa[0], pa[1], pa[2], pa[3]);
+    const double sx = butterfly4_d(px[0], px[1], px[2], px[3]);
+    if ((lane & 15) == 0) {
+      const int row = lane >> 4, e = j + ((row & 1) << 1 | row >> 1);
+      float fr = 0.0f, fa = (float)r2;
+      if (sa != 0.0) {
+        const double f = (-2.0 * r2) / sa;
+        fr = (float)f;
+        fa = (float)(r2 - f * sx);
       }
-      nbr[j] = o;
+      fres[e] = fr;
+      fadd[e] = fa;
     }
   }
+  const uint64_t bm = ballot(bad), rm = ballot(rep);
+  if ((bm | rm) && lane == 0) atomicOr(flag, (bm ? 1 : 0) | (rm ? 2 : 0));
 }
 
 // ------------------------------------------------------------- query side
@@ -1835,11 +1921,17 @@ hipError_t launch_rotate(const float* in, int64_t n, int D, const float* M, floa
 }
 
 hipError_t launch_encode(const float* X, const float* ROT, int64_t N, int D, const int32_t* G, int R,
-                         uint8_t* blocks, int64_t B, hipStream_t st) {
+                         uint8_t* blocks, int64_t B, int* flag, hipStream_t st) {
   const int wpb = 4;
-  dim3 grid((unsigned)((N + wpb - 1) / wpb));
-  hipLaunchKernelGGL(encode_kernel, grid, dim3(64 * wpb), 0, st, X, ROT, N, D, G, R, blocks, B);
-  return hipGetLastError();
+  const dim3 grid((unsigned)((N + wpb - 1) / wpb));
+#define QG_CASE(d)                                                                                                 \
+  if (D == d) {                                                                                                    \
+    hipLaunchKernelGGL(encode_kernel<d>, grid, dim3(64 * wpb), 0, st, X, ROT, N, G, R, blocks, B, flag);           \
+    return hipGetLastError();                                                                                      \
+  }
+  QG_CASE(96) QG_CASE(128) QG_CASE(768) QG_CASE(960)
+#undef QG_CASE
+  return hipErrorInvalidValue;
 }
 
 template <int D, int R, bool GV, int LS, int NB, int LB>
