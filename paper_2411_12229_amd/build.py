@@ -1,9 +1,11 @@
 """Compile libqg.so (HIP kernels + C ABI) for gfx950 with hipcc, in place."""
 from __future__ import annotations
 
+import concurrent.futures
 import os
 import subprocess
 import sys
+import tempfile
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -14,8 +16,10 @@ SOURCES = [os.path.join(CSRC, f) for f in ("qg_kernels.hip", "qg_graph.hip", "qg
 HEADERS = [os.path.join(CSRC, f) for f in ("qg_kernels.h", "qg_graph.h", "qg_layout.h", "qg_internal.h")] + [
     os.path.join(ROOT, "include", "qg.h")]
 
+DIMS = (96, 128, 768, 960)  # the dimensions whose search kernels are built, one object each
+
 FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # every fused multiply-add is written out; division is IEEE correctly rounded
     "-ffp-contract=off", "-fhip-fp32-correctly-rounded-divide-sqrt",
     # no packed fp32 instructions
@@ -24,14 +28,27 @@ FLAGS = [
 ]
 
 
-def build(verbose: bool = False) -> str:
-    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    tmp = LIB + ".tmp"
-    cmd = [hipcc] + FLAGS + ["-I", os.path.join(ROOT, "include"), "-I", CSRC] + SOURCES + ["-o", tmp]
+def _run(cmd) -> str:
     res = subprocess.run(cmd, capture_output=True, text=True)
     err = "\n".join(l for l in res.stderr.splitlines() if "packed-fp32-ops" not in l)
     if res.returncode != 0:
-        raise RuntimeError(f"hipcc failed ({res.returncode}):\n{err}")
+        raise RuntimeError(f"{cmd[0]} failed ({res.returncode}):\n{err}")
+    return err
+
+
+def build(verbose: bool = False) -> str:
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    kernels = SOURCES[0]
+    units = [(kernels, [f"-DQG_DIM={d}"]) for d in DIMS] + [(s, []) for s in SOURCES]
+    tmp = LIB + ".tmp"
+    with tempfile.TemporaryDirectory() as obj:
+        objects = [os.path.join(obj, f"{i}.o") for i in range(len(units))]
+        cmds = [[hipcc] + FLAGS + defs + ["-I", os.path.join(ROOT, "include"), "-I", CSRC, "-c", src, "-o", o]
+                for (src, defs), o in zip(units, objects)]
+        with concurrent.futures.ThreadPoolExecutor(min(8, os.cpu_count() or 1)) as pool:
+            errs = list(pool.map(_run, cmds))
+        errs.append(_run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + objects + ["-o", tmp]))
+    err = "\n".join(e for e in errs if e.strip())
     if verbose and err.strip():
         print(err, file=sys.stderr)
     os.replace(tmp, LIB)

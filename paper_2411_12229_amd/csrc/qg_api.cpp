@@ -84,7 +84,7 @@ struct qg_index {
   int hash_factor = 3;
   int cu_waves = 0;  // cap on resident wavefronts per compute unit (0 = as many as fit)
   int cus = 256;     // compute units of the device (read at creation; sizes the persistent grid)
-  bool beam_regs = true;  // beams of at most 128 entries live in registers (else in LDS)
+  bool beam_regs = true;  // beams of at most 256 entries live in registers (else in LDS)
   bool lut_pad = true;    // LUT layout: a padding row between lane groups (else packed rows)
   bool lut32 = false;     // LUT entries int32 (else int16), for the plain and mixed main pass
   // timing
@@ -506,7 +506,7 @@ static int search_impl(const qg_index* cidx, const float* queries, int64_t nq, i
   int* const counters = fx ? fx->counters : idx->counters;
 
   const int ef_cap = (ef + 3) / 4 * 4;
-  const int k_cap = (k + 3) / 4 * 4;
+  const int k_cap_all = (k + 3) / 4 * 4;
   // visited hash: 2^h >= F ef slots (at least 256), filled to at most one half;
   // queries that visit more finish in the overflow pass.  Past 256 entries the
   // slots grow one per beam entry, not F: a search expands about 0.4-0.6 ef
@@ -533,7 +533,6 @@ static int search_impl(const qg_index* cidx, const float* queries, int64_t nq, i
   a.k_q = k_q;
   a.ef_q = ef_q;
   a.k_out = k;
-  a.k_cap = k_cap;
   a.ef_cap = ef_cap;
   a.hash_bits = hbits;
   a.lut_pad = idx->lut_pad ? 1 : 0;
@@ -564,8 +563,13 @@ static int search_impl(const qg_index* cidx, const float* queries, int64_t nq, i
   // LUT entries: int32 when chosen, for the main pass of the plain and mixed
   // modes (the overflow pass and the other modes keep int16)
   const int lb = (idx->lut32 && (ls == 0 || ls == 3)) ? 4 : 2;
+  const int nb = (idx->beam_regs && !(flags & QG_SEARCH_LDS_BEAM)) ? qgk::beam_regs(false, ls, ef, idx->N) : 0;
+  // NN needs LDS only where it outgrows its registers
+  const int k_cap = k <= 64 * qgk::nn_regs(nb) ? 0 : k_cap_all;
+  const int k_cap_ov = k <= 64 * qgk::nn_regs(0) ? 0 : k_cap_all;
+  a.k_cap = k_cap;
   const qgl::SearchLds L = qgl::search_lds(idx->D, idx->R, ef_cap, 1 << hbits, k_cap, lb);
-  const qgl::SearchLds Lf = qgl::search_lds(idx->D, idx->R, ef_cap, 0, k_cap);
+  const qgl::SearchLds Lf = qgl::search_lds(idx->D, idx->R, ef_cap, 0, k_cap_ov);
   if (L.hash % 16 || L.total % 16)  // the kernels read the hash 16 bytes at a time
     return fail(QG_EUNSUPPORTED, "per-query LDS layout is not 16-byte aligned");
   const size_t lds_cap = 160 * 1024;
@@ -575,7 +579,6 @@ static int search_impl(const qg_index* cidx, const float* queries, int64_t nq, i
   while (wpb > 1 && (size_t)wpb * L.total + extra > lds_cap) wpb >>= 1;
   if ((size_t)L.total + extra > lds_cap) return fail(QG_EUNSUPPORTED, "per-query LDS exceeds the device limit");
   const size_t lds = (size_t)wpb * L.total + extra;
-  const int nb = (idx->beam_regs && !(flags & QG_SEARCH_LDS_BEAM)) ? qgk::beam_regs(false, ls, ef, idx->N) : 0;
   int occ = qgk::search_occupancy(idx->D, idx->R, false, ls, nb, lb, wpb, lds);
   if (occ <= 0) occ = 1;
   if (idx->cu_waves > 0) occ = std::min(occ, std::max(1, idx->cu_waves / wpb));
@@ -592,6 +595,7 @@ static int search_impl(const qg_index* cidx, const float* queries, int64_t nq, i
   HIP_TRY(qgk::launch_search(idx->D, idx->R, false, ls, nb, lb, a, grid, wpb, lds, idx->stream), "search");
   if (!fx && (rc = record(idx, 1, false))) return rc;
   // overflow pass: one wavefront per workgroup, one bitset each
+  a.k_cap = k_cap_ov;
   HIP_TRY(qgk::launch_search(idx->D, idx->R, true, ls, 0, 2, a, idx->fb_slots, 1, (size_t)Lf.total + extra,
                              idx->stream),
           "search overflow pass");

@@ -70,9 +70,12 @@ hipError_t launch_encode(const float* X, const float* ROT, int64_t N, int D, con
 // 3 per-query k and ef (k_q, ef_q set), 4 per-query k and ef with the learned
 // stop (MLP staged in LDS, as for 1), 5 "w/o ME" (the hash holds estimated
 // vertices, not visited ones)
-// nb: beam registers per lane (0: beam in LDS; 1, 2: ef up to 64, 128), as
+// nb: beam registers per lane (0: beam in LDS; 1 .. 4: ef up to 64 nb), as
 // beam_regs() picks for the pass, mode, bound on ef and vector count.
 int beam_regs(bool overflow_pass, int ls_mode, int ef_bound, int64_t n);
+// NN registers per lane of a kernel with nb beam registers (nb 0: beam in LDS);
+// larger k keep NN in LDS
+constexpr int nn_regs(int nb) { return nb >= 3 ? nb : 1; }
 hipError_t launch_search(int D, int R, bool overflow_pass, int ls_mode, int nb, int lb, const SearchArgs& a, int grid,
                          int wpb, size_t lds, hipStream_t st);
 int search_occupancy(int D, int R, bool overflow_pass, int ls_mode, int nb, int lb, int wpb, size_t lds);

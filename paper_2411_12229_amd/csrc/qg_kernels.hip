@@ -3,11 +3,14 @@
 //  rotate_kernel  : Y = X M^T on the matrix cores (fp64 MFMA 16x16x4, k ascending).
 //  encode_kernel  : RaBitQ codes and factors of every edge, one wavefront per vertex.
 //  search_kernel  : Algorithm 1, one query per wavefront; LUT, beam and visited
-//                   hash live in LDS, the top-k in registers (k <= 64) or LDS,
+//                   hash live in LDS, the top-k in registers or LDS,
 //                   vertex blocks stream from HBM.
 //  estimate_kernel: the estimator alone for (query, vertex) pairs.
 //
 // Compiled with -ffp-contract=off: every fused multiply-add below is explicit.
+// The file is compiled once as it is (rotation, encoding, estimator and the
+// dispatch over dimensions) and once per dimension with QG_DIM set to it (that
+// dimension's search kernels), so that the objects build in parallel.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -18,6 +21,7 @@
 
 namespace qgk {
 
+#ifndef QG_DIM
 // Fixed device scratch of the allocation-free search entry point (queue
 // counters, rotated queries, overflow list), one copy per device for as long
 // as the library is loaded.  Host code must not pass `scratch` itself to a
@@ -39,6 +43,7 @@ hipError_t noalloc_scratch(int device, uint8_t** out) {
   *out = addr[device];
   return hipSuccess;
 }
+#endif
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
@@ -183,6 +188,7 @@ __device__ __forceinline__ float exact_dist(const float (&qv)[DPL], const float 
   return butterfly_f(p);
 }
 
+#ifndef QG_DIM
 // ---------------------------------------------------------------- rotation
 
 // out[r][i] = fl32(sum_j M[i][j] in[r][j]), fp64 products accumulated over j
@@ -449,6 +455,8 @@ __global__ __launch_bounds__(256) void encode_kernel(const float* __restrict__ X
   const uint64_t bm = ballot(bad), rm = ballot(rep);
   if ((bm | rm) && lane == 0) atomicOr(flag, (bm ? 1 : 0) | (rm ? 2 : 0));
 }
+
+#endif  // QG_DIM
 
 // ------------------------------------------------------------- query side
 
@@ -902,13 +910,29 @@ __device__ __forceinline__ uint64_t rdlane64(uint64_t v, int l) {
   return ((uint64_t)rdlane((uint32_t)(v >> 32), l) << 32) | rdlane((uint32_t)v, l);
 }
 
-// Element r (wave-uniform) of a small register array, by selects (no dynamic
-// register indexing).
+// Element r of lane l (both wave-uniform) of a small register array: of two
+// registers the selected one's lane; of more, that lane of every register and
+// then scalar selects (a chain of selects between the registers themselves
+// becomes an array in scratch memory).
 template <int NB>
-__device__ __forceinline__ uint64_t pick(const uint64_t (&b)[NB], int r) {
-  uint64_t v = b[0];
+__device__ __forceinline__ uint64_t rdlane64(const uint64_t (&b)[NB], int r, int l) {
+  if constexpr (NB == 2) return rdlane64(r == 1 ? b[1] : b[0], l);
+  uint64_t v = rdlane64(b[0], l);
 #pragma unroll
-  for (int i = 1; i < NB; ++i) v = r == i ? b[i] : v;
+  for (int i = 1; i < NB; ++i) {
+    const uint64_t w = rdlane64(b[i], l);
+    v = r == i ? w : v;
+  }
+  return v;
+}
+template <int NB, class T>
+__device__ __forceinline__ T rdlane(const T (&b)[NB], int r, int l) {
+  T v = rdlane(b[0], l);
+#pragma unroll
+  for (int i = 1; i < NB; ++i) {
+    const T w = rdlane(b[i], l);
+    v = r == i ? w : v;
+  }
   return v;
 }
 
@@ -1489,9 +1513,17 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
   int nvis = 0, nnc = 0, expansions = 0, pops = 0, appended = 0, since = 0;
   float nn_wk = 0.0f;
   uint32_t nn_wi = 0;
-  const bool nn_in_regs = k <= 64;
-  float nrk = 0.0f;
-  uint32_t nri = 0;
+  // NN (ascending (distance, id)): for k <= 64 NK entry 64 r + i is register r
+  // of lane i; larger k keep it in LDS (nkey, nid).
+  constexpr int NK = nn_regs(NB);
+  const bool nn_in_regs = k <= 64 * NK;
+  float nrk[NK];
+  uint32_t nri[NK];
+#pragma unroll
+  for (int r = 0; r < NK; ++r) {
+    nrk[r] = 0.0f;
+    nri[r] = 0;
+  }
   BV nxt;
 
   for (;;) {
@@ -1527,7 +1559,7 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
         if (hole) bw[r] = cbuf[holes + lanes_below(hm)];
         holes += __popcll(hm);
       }
-      if (size == ef) tail = rdlane64(pick<NB>(bw, (ef - 1) >> 6), (ef - 1) & 63) & ~kFlags;
+      if (size == ef) tail = rdlane64<NB>(bw, (ef - 1) >> 6, (ef - 1) & 63) & ~kFlags;
     }
     const float est = __builtin_fmaf(b.fr, (float)S * delta, b.fa + dp);
     const uint64_t cand = pack_kv(est, nb);
@@ -1578,8 +1610,8 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
           mu = ur_;
         }
       }
-      if (rf >= 0) o2f = rdlane64(pick<NB>(bw, rf), first_lane(mf)) & ~kFlags;
-      if (has_stop<LS> && ru >= 0) o2u = rdlane64(pick<NB>(bw, ru), first_lane(mu)) & ~kFlags;
+      if (rf >= 0) o2f = rdlane64<NB>(bw, rf, first_lane(mf)) & ~kFlags;
+      if (has_stop<LS> && ru >= 0) o2u = rdlane64<NB>(bw, ru, first_lane(mu)) & ~kFlags;
     }
 
     // insert p into the visited set: the first empty slot of its probe run
@@ -1641,22 +1673,33 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
     if (nnc < k || kv_less(dp, p, nn_wk, nn_wi)) {
       since = 0;
       if (nn_in_regs) {
-        const int pos = (int)__popcll(ballot(lane < nnc && kv_less(nrk, nri, dp, p)));
+        int pos = 0;
+#pragma unroll
+        for (int r = 0; r < NK; ++r) pos += (int)__popcll(ballot(64 * r + lane < nnc && kv_less(nrk[r], nri[r], dp, p)));
         const int last = nnc < k ? nnc : k - 1;
-        const float upk = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(nrk), 0x138, 0xF, 0xF, false));
-        const uint32_t upi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)nri, 0x138, 0xF, 0xF, false);
-        if (lane > pos && lane <= last) {
-          nrk = upk;
-          nri = upi;
-        }
-        if (lane == pos) {
-          nrk = dp;
-          nri = p;
+#pragma unroll
+        for (int r = NK - 1; r >= 0; --r) {
+          // the entries before, one lane up (DPP shift of the wavefront by one
+          // lane; lane 0 takes lane 63 of the register below)
+          const int ck = r > 0 ? __float_as_int(rdlane(nrk[r > 0 ? r - 1 : 0], 63)) : 0;
+          const int ci = r > 0 ? (int)rdlane(nri[r > 0 ? r - 1 : 0], 63) : 0;
+          const float upk =
+              __int_as_float(__builtin_amdgcn_update_dpp(ck, __float_as_int(nrk[r]), 0x138, 0xF, 0xF, false));
+          const uint32_t upi = (uint32_t)__builtin_amdgcn_update_dpp(ci, (int)nri[r], 0x138, 0xF, 0xF, false);
+          const int e = 64 * r + lane;
+          if (e > pos && e <= last) {
+            nrk[r] = upk;
+            nri[r] = upi;
+          }
+          if (e == pos) {
+            nrk[r] = dp;
+            nri[r] = p;
+          }
         }
         nnc = nnc < k ? nnc + 1 : k;
         if (nnc == k) {
-          nn_wk = rdlane(nrk, k - 1);
-          nn_wi = rdlane(nri, k - 1);
+          nn_wk = rdlane<NK>(nrk, (k - 1) >> 6, (k - 1) & 63);
+          nn_wi = rdlane<NK>(nri, (k - 1) >> 6, (k - 1) & 63);
         }
       } else {
         int pos = 0;
@@ -1744,8 +1787,9 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
     if constexpr (has_stop<LS>) {
       if (expansions >= a.ls_t_min && (expansions - a.ls_t_min) % a.ls_t_every == 0) {
         StopFeatures F;
-        const float nn1 = nn_in_regs ? rdlane(nrk, 0) : uni(nkey[0]);
-        const float nnk = nn_in_regs ? rdlane(nrk, nnc - 1) : uni(nkey[nnc - 1]);
+        const float nn1 = nn_in_regs ? rdlane(nrk[0], 0) : uni(nkey[0]);
+        const float nnk =
+            nn_in_regs ? rdlane<NK>(nrk, (nnc - 1) >> 6, (nnc - 1) & 63) : uni(nkey[nnc - 1]);
         F.compute(expansions, pops, nnc, k, since, de, nn1, nnk, bfk, size, ef, dp, app, R);
         float out;
         if constexpr (mlp_in_lds<LS>)
@@ -1772,15 +1816,24 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
 
   // answer: NN ascending by (distance, id), padded with (-1, inf)
   const int k_out = is_mixed<LS> ? a.k_out : k;
-  for (int i = lane; i < k_out; i += 64) {
-    int32_t id = -1;
-    float d = __builtin_inff();
-    if (i < nnc) {
-      id = nn_in_regs ? (int32_t)nri : (int32_t)nid[i];
-      d = nn_in_regs ? nrk : nkey[i];
+  if (nn_in_regs) {
+#pragma unroll
+    for (int r = 0; r < NK; ++r) {
+      const int i = 64 * r + lane;
+      if (i < k_out) {
+        a.out_ids[q * k_out + i] = i < nnc ? (int32_t)nri[r] : -1;
+        a.out_dists[q * k_out + i] = i < nnc ? nrk[r] : __builtin_inff();
+      }
     }
-    a.out_ids[q * k_out + i] = id;
-    a.out_dists[q * k_out + i] = d;
+    for (int i = 64 * NK + lane; i < k_out; i += 64) {  // a mixed batch's wider rows
+      a.out_ids[q * k_out + i] = -1;
+      a.out_dists[q * k_out + i] = __builtin_inff();
+    }
+  } else {
+    for (int i = lane; i < k_out; i += 64) {
+      a.out_ids[q * k_out + i] = i < nnc ? (int32_t)nid[i] : -1;
+      a.out_dists[q * k_out + i] = i < nnc ? nkey[i] : __builtin_inff();
+    }
   }
   if (a.out_stats && lane == 0) {
     int32_t* st = a.out_stats + 4 * q;
@@ -1792,7 +1845,8 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
 }
 
 // Minimum wavefronts per SIMD the register allocator must allow (1: no
-// constraint).  LDS-beam kernels with D <= 256: 6 for the stop-only and
+// constraint).  Beams of three and four registers at D <= 256: 4 (LDS allows
+// hardly more; at 6 they spill 100-190 bytes).  LDS-beam kernels with D <= 256: 6 for the stop-only and
 // mixed-batch modes.  Register-beam kernels with R = 32, plain or mixed
 // batches, D = 128 (but the one-word plain kernel, which fits in 80 registers
 // anyway) and D = 96: 6, where the allocator would otherwise take 82-96
@@ -1804,6 +1858,7 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
 // bytes of scratch, 1-2% slower); R = 64 would spill over 100 bytes.
 template <int D, int R, int LS, int NB>
 constexpr int waves_hint() {
+  if constexpr (NB > 2) return D <= 256 ? 4 : 1;
   if constexpr (NB > 0) {
     constexpr bool mode = LS == kLsOff || LS == kMixed;
     if constexpr (R == 32 && D == 128 && (LS == kLsStop || LS == kMixedStop)) return 6;
@@ -1857,6 +1912,117 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(waves_hint<
     qi = nwaves + __builtin_amdgcn_readlane(c, 0);
   }
 }
+
+#ifdef QG_DIM
+
+// ------------------------------------------- launchers of one dimension
+
+template <int D, int R, bool GV, int LS, int NB, int LB>
+static hipError_t launch_search_t(const SearchArgs& a, int grid, int wpb, size_t lds, hipStream_t st) {
+  auto kern = search_kernel<D, R, GV, LS, NB, LB>;
+  if (lds > 64 * 1024) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * wpb), lds, st, a);
+  return hipGetLastError();
+}
+
+template <int D, int R, bool GV, int LS, int NB, int LB>
+static int occupancy_t(int wpb, size_t lds) {
+  int nb = 0;
+  auto kern = search_kernel<D, R, GV, LS, NB, LB>;
+  if (lds > 64 * 1024)
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)lds);
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, 64 * wpb, lds) != hipSuccess) return 0;
+  return nb;
+}
+
+struct LaunchOp {
+  const SearchArgs* a;
+  int grid, wpb;
+  size_t lds;
+  hipStream_t st;
+  template <int D, int R, bool GV, int LS, int NB, int LB>
+  hipError_t run() const {
+    return launch_search_t<D, R, GV, LS, NB, LB>(*a, grid, wpb, lds, st);
+  }
+};
+
+struct OccupancyOp {
+  int wpb;
+  size_t lds;
+  template <int D, int R, bool GV, int LS, int NB, int LB>
+  int run() const {
+    return occupancy_t<D, R, GV, LS, NB, LB>(wpb, lds);
+  }
+};
+
+// The kernel instantiation for (D, R), pass, mode, beam storage and LUT
+// entry width.  Register beams (nb 1, 2) exist for the main pass of the
+// plain, stop-only and mixed modes; the traced, "w/o ME" and overflow-pass
+// kernels keep the beam in LDS.  The int32 LUT (lb 4) exists for the main
+// pass of the plain and mixed modes (the ones the autotuner times).
+template <int D, int R, class Op, class Ret>
+static Ret dispatch_mode(bool gv, int ls, int nb, int lb, const Op& op, Ret bad) {
+  if (gv) {
+    if (lb != 2) return bad;
+    switch (ls) {
+      case kLsOff: return op.template run<D, R, true, kLsOff, 0, 2>();
+      case kLsStop: return op.template run<D, R, true, kLsStop, 0, 2>();
+      case kLsTrace: return op.template run<D, R, true, kLsTrace, 0, 2>();
+      case kMixed: return op.template run<D, R, true, kMixed, 0, 2>();
+      case kMixedStop: return op.template run<D, R, true, kMixedStop, 0, 2>();
+      case kNoMe: return op.template run<D, R, true, kNoMe, 0, 2>();
+      default: return bad;
+    }
+  }
+#define QG_NB(ls_, lb_)                                                                         \
+  (nb == 1   ? op.template run<D, R, false, ls_, 1, lb_>()                                      \
+   : nb == 2 ? op.template run<D, R, false, ls_, 2, lb_>()                                      \
+   : nb == 3 ? op.template run<D, R, false, ls_, 3, lb_>()                                      \
+   : nb == 4 ? op.template run<D, R, false, ls_, 4, lb_>() : op.template run<D, R, false, ls_, 0, lb_>())
+  if (lb == 4) {
+    switch (ls) {
+      case kLsOff: return QG_NB(kLsOff, 4);
+      case kMixed: return QG_NB(kMixed, 4);
+      default: return bad;
+    }
+  }
+  if (lb != 2) return bad;
+  switch (ls) {
+    case kLsOff: return QG_NB(kLsOff, 2);
+    case kLsStop: return QG_NB(kLsStop, 2);
+    case kLsTrace: return op.template run<D, R, false, kLsTrace, 0, 2>();
+    case kMixed: return QG_NB(kMixed, 2);
+    case kMixedStop: return QG_NB(kMixedStop, 2);
+    case kNoMe: return op.template run<D, R, false, kNoMe, 0, 2>();
+    default: return bad;
+  }
+#undef QG_NB
+}
+
+#define QG_JOIN2(a, b) a##b
+#define QG_JOIN(a, b) QG_JOIN2(a, b)
+
+hipError_t QG_JOIN(launch_search_, QG_DIM)(int R, bool overflow_pass, int ls_mode, int nb, int lb, const SearchArgs& a,
+                                           int grid, int wpb, size_t lds, hipStream_t st) {
+  const LaunchOp op{&a, grid, wpb, lds, st};
+  if (R == 32) return dispatch_mode<QG_DIM, 32>(overflow_pass, ls_mode, nb, lb, op, hipErrorInvalidValue);
+  if (R == 64) return dispatch_mode<QG_DIM, 64>(overflow_pass, ls_mode, nb, lb, op, hipErrorInvalidValue);
+  return hipErrorInvalidValue;
+}
+
+int QG_JOIN(search_occupancy_, QG_DIM)(int R, bool overflow_pass, int ls_mode, int nb, int lb, int wpb, size_t lds) {
+  const OccupancyOp op{wpb, lds};
+  if (R == 32) return dispatch_mode<QG_DIM, 32>(overflow_pass, ls_mode, nb, lb, op, 0);
+  if (R == 64) return dispatch_mode<QG_DIM, 64>(overflow_pass, ls_mode, nb, lb, op, 0);
+  return 0;
+}
+
+#else  // QG_DIM
 
 // -------------------------------------------------------------- estimator
 
@@ -1934,116 +2100,43 @@ hipError_t launch_encode(const float* X, const float* ROT, int64_t N, int D, con
   return hipErrorInvalidValue;
 }
 
-template <int D, int R, bool GV, int LS, int NB, int LB>
-static hipError_t launch_search_t(const SearchArgs& a, int grid, int wpb, size_t lds, hipStream_t st) {
-  auto kern = search_kernel<D, R, GV, LS, NB, LB>;
-  if (lds > 64 * 1024) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * wpb), lds, st, a);
-  return hipGetLastError();
-}
-
-template <int D, int R, bool GV, int LS, int NB, int LB>
-static int occupancy_t(int wpb, size_t lds) {
-  int nb = 0;
-  auto kern = search_kernel<D, R, GV, LS, NB, LB>;
-  if (lds > 64 * 1024)
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)lds);
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, 64 * wpb, lds) != hipSuccess) return 0;
-  return nb;
-}
-
-struct LaunchOp {
-  const SearchArgs* a;
-  int grid, wpb;
-  size_t lds;
-  hipStream_t st;
-  template <int D, int R, bool GV, int LS, int NB, int LB>
-  hipError_t run() const {
-    return launch_search_t<D, R, GV, LS, NB, LB>(*a, grid, wpb, lds, st);
-  }
-};
-
-struct OccupancyOp {
-  int wpb;
-  size_t lds;
-  template <int D, int R, bool GV, int LS, int NB, int LB>
-  int run() const {
-    return occupancy_t<D, R, GV, LS, NB, LB>(wpb, lds);
-  }
-};
-
-// The kernel instantiation for (D, R), pass, mode, beam storage and LUT
-// entry width.  Register beams (nb 1, 2) exist for the main pass of the
-// plain, stop-only and mixed modes; the traced, "w/o ME" and overflow-pass
-// kernels keep the beam in LDS.  The int32 LUT (lb 4) exists for the main
-// pass of the plain and mixed modes (the ones the autotuner times).
-template <int D, int R, class Op, class Ret>
-static Ret dispatch_mode(bool gv, int ls, int nb, int lb, const Op& op, Ret bad) {
-  if (gv) {
-    if (lb != 2) return bad;
-    switch (ls) {
-      case kLsOff: return op.template run<D, R, true, kLsOff, 0, 2>();
-      case kLsStop: return op.template run<D, R, true, kLsStop, 0, 2>();
-      case kLsTrace: return op.template run<D, R, true, kLsTrace, 0, 2>();
-      case kMixed: return op.template run<D, R, true, kMixed, 0, 2>();
-      case kMixedStop: return op.template run<D, R, true, kMixedStop, 0, 2>();
-      case kNoMe: return op.template run<D, R, true, kNoMe, 0, 2>();
-      default: return bad;
-    }
-  }
-#define QG_NB(ls_, lb_)                                                                         \
-  (nb == 1 ? op.template run<D, R, false, ls_, 1, lb_>()                                        \
-           : nb == 2 ? op.template run<D, R, false, ls_, 2, lb_>() : op.template run<D, R, false, ls_, 0, lb_>())
-  if (lb == 4) {
-    switch (ls) {
-      case kLsOff: return QG_NB(kLsOff, 4);
-      case kMixed: return QG_NB(kMixed, 4);
-      default: return bad;
-    }
-  }
-  if (lb != 2) return bad;
-  switch (ls) {
-    case kLsOff: return QG_NB(kLsOff, 2);
-    case kLsStop: return QG_NB(kLsStop, 2);
-    case kLsTrace: return op.template run<D, R, false, kLsTrace, 0, 2>();
-    case kMixed: return QG_NB(kMixed, 2);
-    case kMixedStop: return QG_NB(kMixedStop, 2);
-    case kNoMe: return op.template run<D, R, false, kNoMe, 0, 2>();
-    default: return bad;
-  }
-#undef QG_NB
-}
-
-// Measured on the SIFT-shaped 1M x 128 index (10,000 queries): one beam
-// register is 11-14% faster than the LDS beam in the plain, mixed and
-// stop-only kernels; two registers tie with it in the plain and mixed kernels
-// and lose 6% in the stop-only kernel (whose MLP already holds many registers).
+// Beam registers per lane for a bound on ef.  Measured, register beam against
+// LDS beam in one call: one register (ef 48, 1M x 128, 10,000 queries) 11-14%
+// faster in the plain, mixed and stop-only kernels; two tie or win in the plain
+// and mixed kernels and lose 6% in the stop-only kernel (whose MLP already
+// holds many registers); three (ef 192, 300,000 x 96) 293 against 386 us for
+// one query, 538 against 660 us for 3,001 queries, 1,251 against 1,376 us for
+// 10,000; four (ef 250) 413 against 518, 778 against 893 and 1,767 against
+// 1,845 us.  The LDS merge's binary searches are a chain of dependent reads,
+// the register merge one pass over the candidates.
 int beam_regs(bool overflow_pass, int ls_mode, int ef_bound, int64_t n) {
   if (overflow_pass || ls_mode == kLsTrace || ls_mode == kNoMe || n > (int64_t)kIdMask30) return 0;
   if (ef_bound <= 64) return 1;
-  return (ef_bound <= 128 && (ls_mode == kLsOff || ls_mode == kMixed)) ? 2 : 0;
+  if (ls_mode != kLsOff && ls_mode != kMixed) return 0;
+  return ef_bound <= 256 ? (ef_bound + 63) / 64 : 0;
 }
+
+#define QG_DIMS(X) X(96) X(128) X(768) X(960)
+#define QG_DECL(d)                                                                                            \
+  hipError_t launch_search_##d(int R, bool overflow_pass, int ls_mode, int nb, int lb, const SearchArgs& a,   \
+                               int grid, int wpb, size_t lds, hipStream_t st);                                \
+  int search_occupancy_##d(int R, bool overflow_pass, int ls_mode, int nb, int lb, int wpb, size_t lds);
+QG_DIMS(QG_DECL)
+#undef QG_DECL
 
 hipError_t launch_search(int D, int R, bool overflow_pass, int ls_mode, int nb, int lb, const SearchArgs& a,
                          int grid, int wpb, size_t lds, hipStream_t st) {
-  const LaunchOp op{&a, grid, wpb, lds, st};
-#define QG_CASE(d, r) \
-  if (D == d && R == r) return dispatch_mode<d, r>(overflow_pass, ls_mode, nb, lb, op, hipErrorInvalidValue);
-  QG_SHAPES(QG_CASE)
+#define QG_CASE(d) \
+  if (D == d) return launch_search_##d(R, overflow_pass, ls_mode, nb, lb, a, grid, wpb, lds, st);
+  QG_DIMS(QG_CASE)
 #undef QG_CASE
   return hipErrorInvalidValue;
 }
 
 int search_occupancy(int D, int R, bool overflow_pass, int ls_mode, int nb, int lb, int wpb, size_t lds) {
-  const OccupancyOp op{wpb, lds};
-#define QG_CASE(d, r) \
-  if (D == d && R == r) return dispatch_mode<d, r>(overflow_pass, ls_mode, nb, lb, op, 0);
-  QG_SHAPES(QG_CASE)
+#define QG_CASE(d) \
+  if (D == d) return search_occupancy_##d(R, overflow_pass, ls_mode, nb, lb, wpb, lds);
+  QG_DIMS(QG_CASE)
 #undef QG_CASE
   return 0;
 }
@@ -2059,5 +2152,7 @@ hipError_t launch_estimate(int D, int R, const EstimateArgs& a, int64_t nq, hipS
 #undef QG_CASE
   return hipErrorInvalidValue;
 }
+
+#endif  // QG_DIM
 
 }  // namespace qgk

@@ -1,0 +1,71 @@
+"""Searches at the edges of the beam's and the result list's register counts
+(64 entries a register), against the oracle, through the C ABI."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2411_12229_amd import qg  # noqa: E402
+
+DEV = torch.device("cuda:0")
+
+
+def T(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+
+
+@pytest.fixture(scope="module")
+def made():
+    cache = {}
+
+    def get(D, R, n=1500, nq=40):
+        if (D, R) not in cache:
+            g = np.random.Generator(np.random.PCG64(D + R))
+            c = g.standard_normal((12, D))
+            X = (c[g.integers(0, 12, n)] + 0.5 * g.standard_normal((n, D))).astype(np.float32)
+            Q = (c[g.integers(0, 12, nq)] + 0.5 * g.standard_normal((nq, D))).astype(np.float32)
+            M, G, e = synth.rotation(D, 3), synth.knn_graph(X, R, 4), synth.medoid(X)
+            idx = qg.qg_build_index(T(X), T(G), T(M), e)
+            cache[D, R] = (idx, oracle.encode(X, G, M), M, e, Q)
+        return cache[D, R]
+
+    return get
+
+
+@pytest.mark.parametrize("D,R", [(96, 32), (128, 64), (960, 64)])
+@pytest.mark.parametrize("k,ef", [
+    (10, 64), (10, 65), (65, 128), (128, 129), (129, 192), (192, 193), (193, 256), (256, 256), (257, 256),
+    (300, 193), (10, 257), (64, 130), (1, 255),
+])
+def test_equals_oracle(made, D, R, k, ef):
+    idx, blocks, M, e, Q = made(D, R)
+    print(f"D={D} R={R} k={k} ef={ef}", flush=True)
+    oi, od, os_ = oracle.search(blocks, D, R, e, M, Q, k, ef, with_stats=True)
+    for flags in (0, qg.QG_SEARCH_SMALL_HASH, qg.QG_SEARCH_LDS_BEAM):
+        ids, dists, st = idx.search(T(Q), k, ef, flags=flags, stats=True)
+        assert np.array_equal(ids.cpu().numpy(), oi) and np.array_equal(dists.cpu().numpy(), od)
+        assert np.array_equal(st.cpu().numpy()[:, :3], os_[:, :3])
+
+
+@pytest.mark.parametrize("D,R", [(96, 32), (960, 64)])
+@pytest.mark.parametrize("k_max,ef_max", [(300, 200), (100, 192), (260, 256)])
+def test_mixed_rows_equal_oracle(made, D, R, k_max, ef_max):
+    """Per-query settings over the whole range of one launch, output rows wider than the registers hold."""
+    idx, blocks, M, e, Q = made(D, R)
+    ks = np.array([1, 10, 64, 65, min(129, k_max), k_max], np.int32)[np.arange(len(Q)) % 6]
+    efs = np.array([1, 64, 65, 130, ef_max], np.int32)[np.arange(len(Q)) % 5]
+    print(f"mixed D={D} R={R} k_max={k_max} ef_max={ef_max}", flush=True)
+    ids, dists = idx.search_mixed(T(Q), T(ks), T(efs), k_max=k_max, ef_max=ef_max)
+    ids, dists = ids.cpu().numpy(), dists.cpu().numpy()
+    for i in range(len(Q)):
+        k = int(ks[i])
+        oi, od = oracle.search(blocks, D, R, e, M, Q[i:i + 1], k, int(efs[i]))
+        assert np.array_equal(ids[i, :k], oi[0]) and np.array_equal(dists[i, :k], od[0])
+        assert (ids[i, k:] == -1).all() and np.isinf(dists[i, k:]).all()
