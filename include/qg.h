@@ -225,7 +225,9 @@ int qg_set_stream(qg_index *idx, void *hip_stream);
  * table of Sec. 2.2's FastScan, rows of 16 entries: int16 or int32 entries,
  * with a padding row between the lane groups that share a neighbour, so that
  * their lookups fall in different LDS banks, or with packed rows; int32
- * entries apply to the plain and mixed searches).  The fastest setting is kept for
+ * entries apply to the plain and mixed searches; only D = 128, R = 32 searches
+ * through a table, the other shapes sum over bit planes of the query and the
+ * layout has no effect on them).  The fastest setting is kept for
  * later searches of this index.  Each setting is timed as the median of seven
  * calls after one untimed call.  Results do not depend on the choice, only
  * the speed.  Outputs (host, nullable): the chosen wavefronts per workgroup,

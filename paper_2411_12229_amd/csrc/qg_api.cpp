@@ -561,8 +561,9 @@ static int search_impl(const qg_index* cidx, const float* queries, int64_t nq, i
   }
 
   // LUT entries: int32 when chosen, for the main pass of the plain and mixed
-  // modes (the overflow pass and the other modes keep int16)
-  const int lb = (idx->lut32 && (ls == 0 || ls == 3)) ? 4 : 2;
+  // modes (the overflow pass and the other modes keep int16; shapes that sum
+  // over bit planes have no table)
+  const int lb = (idx->lut32 && (ls == 0 || ls == 3) && !qgl::use_planes(idx->D, idx->R)) ? 4 : 2;
   const int nb = (idx->beam_regs && !(flags & QG_SEARCH_LDS_BEAM)) ? qgk::beam_regs(false, ls, ef, idx->N) : 0;
   // NN needs LDS only where it outgrows its registers
   const int k_cap = k <= 64 * qgk::nn_regs(nb) ? 0 : k_cap_all;
@@ -719,9 +720,9 @@ static int autotune_impl(qg_index* idx, int64_t nq, int32_t kcap, int32_t ef_bou
     }
   }
   // the other LUT layouts (packed int16 rows, padded and packed int32 rows)
-  // for the best setting so far
+  // for the best setting so far, for the shapes that have a table
   for (int layout : {0, 3, 2}) {
-    if (rc) break;
+    if (rc || qgl::use_planes(idx->D, idx->R)) break;
     idx->cu_waves = best_cw;
     idx->beam_regs = best_beam;
     idx->lut_pad = (layout & 1) != 0;

@@ -2,7 +2,7 @@
 //
 //  rotate_kernel  : Y = X M^T on the matrix cores (fp64 MFMA 16x16x4, k ascending).
 //  encode_kernel  : RaBitQ codes and factors of every edge, one wavefront per vertex.
-//  search_kernel  : Algorithm 1, one query per wavefront; LUT, beam and visited
+//  search_kernel  : Algorithm 1, one query per wavefront; the quantised query and visited
 //                   hash live in LDS, the top-k in registers or LDS,
 //                   vertex blocks stream from HBM.
 //  estimate_kernel: the estimator alone for (query, vertex) pairs.
@@ -507,6 +507,58 @@ __device__ __forceinline__ float build_lut(const float* __restrict__ qrot, void*
   return delta;
 }
 
+// The quantised query as bit planes (the same q_s and Delta as build_lut): for
+// every 32 dims eight words, the signs and then bits 6 .. 0 of |q_s|, and in
+// qsum the sum of |q_s|.  A neighbour's sum over its code bits b,
+// S = sum (2b - 1) q_s, is then 2 sum_p 2^p popcount((b ^ sign) & plane_p) -
+// qsum: whole numbers, equal to the table's sums.
+template <int D>
+__device__ __forceinline__ float build_planes(const float* __restrict__ qrot, uint32_t* planes, int& qsum) {
+  constexpr int DPL = (D + 63) / 64;
+  const int lane = lane_id();
+  float m = 0.0f;
+  for (int i = lane; i < D; i += 64) m = fmaxf(m, __builtin_fabsf(qrot[i]));
+  m = wave_max(m);
+  float inv = 0.0f, delta = 0.0f;
+  if (m != 0.0f) {
+    inv = 127.0f / m;
+    delta = m / 127.0f;
+  }
+  int sum = 0;
+#pragma unroll 1
+  for (int t = 0; t < DPL; ++t) {
+    const int i = lane + 64 * t;
+    float v = (m != 0.0f && i < D) ? __builtin_rintf(qrot[i < D ? i : 0] * inv) : 0.0f;
+    v = fminf(fmaxf(v, -127.0f), 127.0f);
+    const int s = (int)v, a = s < 0 ? -s : s;
+    uint64_t w[8];
+    w[0] = ballot(s < 0);
+#pragma unroll
+    for (int p = 0; p < 7; ++p) {
+      w[7 - p] = ballot((a >> p) & 1);
+      sum += (int)__popcll(w[7 - p]) << p;
+    }
+    if (lane == 0) {
+      uint4* o = reinterpret_cast<uint4*>(planes + 16 * t);
+      o[0] = make_uint4((uint32_t)w[0], (uint32_t)w[1], (uint32_t)w[2], (uint32_t)w[3]);
+      o[1] = make_uint4((uint32_t)w[4], (uint32_t)w[5], (uint32_t)w[6], (uint32_t)w[7]);
+      o[2] = make_uint4((uint32_t)(w[0] >> 32), (uint32_t)(w[1] >> 32), (uint32_t)(w[2] >> 32), (uint32_t)(w[3] >> 32));
+      o[3] = make_uint4((uint32_t)(w[4] >> 32), (uint32_t)(w[5] >> 32), (uint32_t)(w[6] >> 32), (uint32_t)(w[7] >> 32));
+    }
+  }
+  qsum = uni(sum);
+  wave_sync();
+  return delta;
+}
+
+// The query's FastScan data in LDS, whichever form the shape uses.
+template <int D, int R, int LB>
+__device__ __forceinline__ float build_query(const float* __restrict__ qrot, void* lut, int pad, int& qsum) {
+  if constexpr (qgl::use_planes(D, R)) return build_planes<D>(qrot, static_cast<uint32_t*>(lut), qsum);
+  qsum = 0;
+  return build_lut<D, R, LB>(qrot, lut, pad);
+}
+
 // Vertex block fields as one lane sees them: its dims of the raw vector, its
 // share of one neighbour's code, that neighbour's factors and id.
 // LDS (address space 3) views: 32-bit byte addresses of shared memory.
@@ -552,14 +604,26 @@ __device__ __forceinline__ int lut_sum(uint32_t b8, uint32_t ev, uint32_t od) {
     return v;
 }
 
+// acc + the number of bits set in x, in one instruction (the compiler would
+// count words apart and add the counts).
+__device__ __forceinline__ int bcnt(uint32_t x, int acc) {
+  int r;
+  asm("v_bcnt_u32_b32 %0, %1, %2" : "=v"(r) : "v"(x), "v"(acc));
+  return r;
+}
+
 template <int D, int R>
 struct BlockView {
   static constexpr int LPN = 64 / R;        // lanes per neighbour
   static constexpr int CB = D / 8;          // code bytes per neighbour
   static constexpr int BPL = CB / LPN;      // code bytes per lane
   static constexpr int DPL = (D + 63) / 64; // raw dims per lane
-  static constexpr bool WORDS = (BPL % 4) == 0;
-  static constexpr int NW = WORDS ? BPL / 4 : BPL / 2;  // 32- or 16-bit code units per lane
+  static constexpr bool PLANES = qgl::use_planes(D, R);
+  static constexpr bool WORDS = PLANES || (BPL % 4) == 0;
+  // 32- or 16-bit code units per lane; with bit planes the D / 32 words of a
+  // code are split over its lanes, rounded up (a lane past the end repeats the
+  // last word against empty planes)
+  static constexpr int NW = PLANES ? (D / 32 + LPN - 1) / LPN : WORDS ? BPL / 4 : BPL / 2;
   // Whether a second block (the next vertex, prefetched) is held in registers
   // beside this one (every shape built here: at most 45 words per lane);
   // wider shapes would load the block when it is used instead.
@@ -577,8 +641,14 @@ struct BlockView {
       x[t] = (i < D) ? raw[i] : 0.0f;
     }
     const int j = lane / LPN, h = lane % LPN;
-    const uint8_t* cp = blk + qgl::off_codes(D) + j * CB + h * BPL;
-    if constexpr (WORDS) {
+    const uint8_t* cp = blk + qgl::off_codes(D) + j * CB + (PLANES ? 0 : h * BPL);
+    if constexpr (PLANES) {
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const int i = h * NW + w;
+        cw[w] = reinterpret_cast<const uint32_t*>(cp)[LPN * NW == D / 32 || i < D / 32 ? i : D / 32 - 1];
+      }
+    } else if constexpr (WORDS) {
 #pragma unroll
       for (int w = 0; w < NW; ++w) cw[w] = reinterpret_cast<const uint32_t*>(cp)[w];
     } else {
@@ -590,10 +660,96 @@ struct BlockView {
     nb = reinterpret_cast<const int32_t*>(blk + qgl::off_nbr(D, R))[j];
   }
 
+  // The sum from bit planes: a word costs seven ANDs and seven counts that
+  // accumulate; its eight plane words come as two 16-byte LDS reads at one
+  // address per lane group (a table lookup per four dims is 8 reads of 2 bytes
+  // a word).  The next two words' planes are read while these two are counted.
+  __device__ __forceinline__ int popscan(const uint4* planes, int lane, int qsum) const {
+    const uint4* P = planes + (LPN == 2 ? (lane & 1) * 2 * NW : 0);
+    if constexpr (NW <= 4) {
+      // short codes: from the highest plane down, the sum doubled between
+      // planes (one register instead of seven)
+      uint32_t c[NW];
+      int s = 0;
+      uint4 a[NW];
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        a[w] = P[2 * w];
+        c[w] = cw[w] ^ a[w].x;
+      }
+#pragma unroll
+      for (int w = 0; w < NW; ++w) s = bcnt(c[w] & a[w].y, s);
+      s += s;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) s = bcnt(c[w] & a[w].z, s);
+      s += s;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) s = bcnt(c[w] & a[w].w, s);
+#pragma unroll
+      for (int w = 0; w < NW; ++w) a[w] = P[2 * w + 1];
+      s += s;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) s = bcnt(c[w] & a[w].x, s);
+      s += s;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) s = bcnt(c[w] & a[w].y, s);
+      s += s;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) s = bcnt(c[w] & a[w].z, s);
+      s += s;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) s = bcnt(c[w] & a[w].w, s);
+      if constexpr (LPN == 2) s += xor_lane_i<1>(s);
+      return 2 * s - qsum;
+    }
+    int acc[7] = {0, 0, 0, 0, 0, 0, 0};
+    constexpr int G = 2;  // words a step
+    uint4 buf[2][2 * G];
+    auto fetch = [&](int s, uint4* o) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < 2 * G; ++i)
+        if (G * s + i / 2 < NW) o[i] = P[2 * G * s + i];
+    };
+    fetch(0, buf[0]);
+#pragma unroll
+    for (int s = 0; s < (NW + G - 1) / G; ++s) {
+      if (G * (s + 1) < NW) fetch(s + 1, buf[(s + 1) & 1]);
+      // wide codes: no further planes are read before this step's are counted
+      // (the memory clobber holds the reads, the first count the order)
+      if constexpr (NW > 4) asm volatile("" : "+v"(acc[0])::"memory");
+#pragma unroll
+      for (int i = 0; i < G; ++i)
+        if (G * s + i < NW) {
+          const uint4 a = buf[s & 1][2 * i], b = buf[s & 1][2 * i + 1];
+          const uint32_t c = cw[G * s + i] ^ a.x;
+          acc[6] = bcnt(c & a.y, acc[6]);
+          acc[5] = bcnt(c & a.z, acc[5]);
+          acc[4] = bcnt(c & a.w, acc[4]);
+          acc[3] = bcnt(c & b.x, acc[3]);
+          acc[2] = bcnt(c & b.y, acc[2]);
+          acc[1] = bcnt(c & b.z, acc[1]);
+          acc[0] = bcnt(c & b.w, acc[0]);
+        }
+      if constexpr (NW > 4) {
+        asm volatile(""
+                     : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5]), "+v"(acc[6])
+                     :
+                     : "memory");
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    int s = acc[6];
+#pragma unroll
+    for (int p = 5; p >= 0; --p) s = 2 * s + acc[p];
+    if constexpr (LPN == 2) s += xor_lane_i<1>(s);
+    return 2 * s - qsum;
+  }
+
   // FastScan sum of this lane's nibbles; the LPN lanes of one neighbour are
   // then combined (integer, exact) so every lane holds S_j.
   template <int LB = 2>
-  __device__ __forceinline__ int fastscan(const void* lut, int lane, int pad) const {
+  __device__ __forceinline__ int fastscan(const void* lut, int lane, int pad, int qsum) const {
+    if constexpr (PLANES) return popscan(static_cast<const uint4*>(lut), lane, qsum);
     constexpr int RPG = D / 4 / LPN;
     constexpr int UNIT_NIB = WORDS ? 8 : 4;
     const int h = lane % LPN;
@@ -1009,7 +1165,8 @@ __device__ void search_one(const SearchArgs& a, int64_t q, uint8_t* lds, const q
       return exact_dist<DPL>(qv, xv);
     }
   };
-  const float delta = build_lut<D, R, LB>(a.qrot + q * D, lut, a.lut_pad);
+  int qsum;
+  const float delta = build_query<D, R, LB>(a.qrot + q * D, lut, a.lut_pad, qsum);
 
   // S starts with the entry, keyed by its exact distance (no estimate exists for it).
   float de;
@@ -1121,7 +1278,7 @@ __device__ void search_one(const SearchArgs& a, int64_t q, uint8_t* lds, const q
     const float dp = uni(dist(b.x));
 
     // FastScan estimates of all neighbours (Eq. normalization with Eq. 3.1)
-    const int S = b.template fastscan<LB>(lut, lane, a.lut_pad);
+    const int S = b.template fastscan<LB>(lut, lane, a.lut_pad, qsum);
     const float est = __builtin_fmaf(b.fr, (float)S * delta, b.fa + dp);
     const uint32_t nb = (uint32_t)b.nb;
     const uint64_t cand = pack_kv(est, nb);
@@ -1493,7 +1650,8 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
       return exact_dist<DPL>(qv, xv);
     }
   };
-  const float delta = build_lut<D, R, LB>(a.qrot + q * D, lut, a.lut_pad);
+  int qsum;
+  const float delta = build_query<D, R, LB>(a.qrot + q * D, lut, a.lut_pad, qsum);
 
   // the entry starts the beam, keyed by its exact distance; it is the first
   // vertex expanded, so its block serves both
@@ -1547,7 +1705,7 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
     uint32_t ns = vis.slot4(probe ? nb : 0u);
     uint4 ne = vis.group(ns);
     // FastScan estimates of all neighbours (Eq. normalization with Eq. 3.1)
-    const int S = b.template fastscan<LB>(lut, lane, a.lut_pad);
+    const int S = b.template fastscan<LB>(lut, lane, a.lut_pad, qsum);
     // finish the pending merge: range slots still holding the sentinel take
     // the candidates in rank order
     if (pending) {
@@ -1862,7 +2020,7 @@ constexpr int waves_hint() {
   if constexpr (NB > 0) {
     constexpr bool mode = LS == kLsOff || LS == kMixed;
     if constexpr (R == 32 && D == 128 && (LS == kLsStop || LS == kMixedStop)) return 6;
-    if constexpr (R == 32 && D == 128) return mode && !(NB == 1 && LS == kLsOff) ? 6 : 1;
+    if constexpr (R == 32 && D == 128) return mode ? 6 : 1;
     if constexpr (R == 32 && D == 96) return mode ? 6 : 1;
     return 1;
   }
@@ -1985,7 +2143,8 @@ static Ret dispatch_mode(bool gv, int ls, int nb, int lb, const Op& op, Ret bad)
    : nb == 3 ? op.template run<D, R, false, ls_, 3, lb_>()                                      \
    : nb == 4 ? op.template run<D, R, false, ls_, 4, lb_>() : op.template run<D, R, false, ls_, 0, lb_>())
   if (lb == 4) {
-    switch (ls) {
+    if constexpr (qgl::use_planes(D, R)) return bad;
+    else switch (ls) {
       case kLsOff: return QG_NB(kLsOff, 4);
       case kMixed: return QG_NB(kMixed, 4);
       default: return bad;
@@ -2033,7 +2192,8 @@ __global__ __launch_bounds__(64) void estimate_kernel(EstimateArgs a) {
   const int lane = lane_id();
   const int64_t q = blockIdx.x;
   int16_t* lut = reinterpret_cast<int16_t*>(smem);
-  const float delta = build_lut<D, R>(a.qrot + q * D, lut, a.lut_pad);
+  int qsum;
+  const float delta = build_query<D, R, 2>(a.qrot + q * D, lut, a.lut_pad, qsum);
   float qv[BV::DPL];
   for (int t = 0; t < BV::DPL; ++t) {
     const int i = lane + 64 * t;
@@ -2042,7 +2202,7 @@ __global__ __launch_bounds__(64) void estimate_kernel(EstimateArgs a) {
   BV b;
   b.load(a.blocks + (int64_t)a.vertex[q] * a.block_bytes, lane);
   const float dp = exact_dist<BV::DPL>(qv, b.x);
-  const int S = b.fastscan(lut, lane, a.lut_pad);
+  const int S = b.fastscan(lut, lane, a.lut_pad, qsum);
   const float est = __builtin_fmaf(b.fr, (float)S * delta, b.fa + dp);
   if (lane % BV::LPN == 0) {
     a.out_S[q * R + lane / BV::LPN] = S;
@@ -2142,7 +2302,7 @@ int search_occupancy(int D, int R, bool overflow_pass, int ls_mode, int nb, int 
 }
 
 hipError_t launch_estimate(int D, int R, const EstimateArgs& a, int64_t nq, hipStream_t st) {
-  const size_t lds = (size_t)qgl::align16(qgl::lut_rows_padded(D, R) * 32);
+  const size_t lds = (size_t)qgl::query_bytes(D, R, 2);
 #define QG_CASE(d, r)                                                                           \
   if (D == d && R == r) {                                                                       \
     hipLaunchKernelGGL((estimate_kernel<d, r>), dim3((unsigned)nq), dim3(64), lds, st, a);      \

@@ -32,10 +32,26 @@ __host__ __device__ constexpr int align16(int x) { return (x + 15) & ~15; }
 // Wide vectors keep the raw query in LDS instead of registers.
 __host__ __device__ constexpr bool query_in_lds(int D) { return D > 256; }
 
-// LUT rows are 16 int16 entries (32 bytes).  With two lanes per neighbour the
+// Where the query's FastScan data is a table (use_planes): LUT rows are 16 int16 entries (32 bytes).  With two lanes per neighbour the
 // second lane's rows start one padding row later so that the two halves of a
 // wavefront read different LDS banks.
 __host__ __device__ constexpr int lut_rows_padded(int D, int R) { return D / 4 + (64 / R) - 1; }
+
+// Whether a shape sums codes against the query's bit planes instead of a table:
+// all but D = 128, R = 32.  Measured, table against planes, k 10: 960 x 64, 37
+// queries at ef 128 475 against 358 us; 960 x 32, 10,000 queries at ef 48 1,259
+// against 960 us; 768 x 64, 1,000 queries at ef 96 323 against 262 us; 96 x 32,
+// 1,000 at ef 48 148 against 131 us; 128 x 64, 10,000 at ef 48 291 against 262
+// us; no shape slower at 1, 1,000 or 10,000 queries and ef 16 to 128.  At 128 x
+// 32 (two words a lane) the two tie at ef 48 and planes lose 1-2% at ef 96,
+// 60,000 queries (four registers spilled instead of two).
+__host__ __device__ constexpr bool use_planes(int D, int R) { return !(D == 128 && R == 32); }
+
+// Bytes of the query's FastScan data: 64 a chunk of 64 dims as bit planes, or
+// the table.
+__host__ __device__ constexpr int query_bytes(int D, int R, int lut_entry_bytes) {
+  return use_planes(D, R) ? (D + 63) / 64 * 64 : align16(lut_rows_padded(D, R) * 16 * lut_entry_bytes);
+}
 
 // cand: one expansion's candidates (R words + 4 of padding), reused for their
 // insertion points; beam: packed (key, id | checked) words kept sorted; hash:
@@ -51,7 +67,7 @@ __host__ __device__ inline SearchLds search_lds(int D, int R, int ef_cap, int ha
                                                 int lut_entry_bytes = 2) {
   SearchLds s{};
   int o = 0;
-  s.lut = o;   o += align16(lut_rows_padded(D, R) * 16 * lut_entry_bytes);
+  s.lut = o;   o += query_bytes(D, R, lut_entry_bytes);
   s.cand = o;  o += 8 * (R + 4);
   s.beam = o;  o += 8 * ef_cap;
   s.hash = o;  o += 4 * hash_cap;
