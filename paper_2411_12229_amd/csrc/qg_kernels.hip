@@ -63,7 +63,17 @@ __device__ __forceinline__ int lanes_below(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-__device__ __forceinline__ int first_lane(uint64_t m) { return __ffsll((unsigned long long)m) - 1; }
+__device__ __forceinline__ int first_lane(uint64_t m) { return __builtin_ctzll(m); }  // m != 0
+
+// Lane predicates as 64-bit masks in scalar registers: `lanes` turns a mask back
+// into a predicate (no instruction: the mask is the select's or the branch's
+// operand), so conditions are combined by scalar instructions, and ballot is
+// only ever taken of a single compare (of anything else it costs two more
+// vector instructions).
+__device__ __forceinline__ bool lanes(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+// Lanes below n (any n): one compare (shifting a mask to length costs six
+// scalar instructions with the ends of the range).
+__device__ __forceinline__ uint64_t mask_below(int n) { return ballot(lane_id() < n); }
 
 __device__ __forceinline__ void wave_sync() { __builtin_amdgcn_wave_barrier(); }
 
@@ -800,11 +810,11 @@ struct Visited {
   __device__ __forceinline__ uint32_t slot4(uint32_t id) const { return slot0(id) & ~3u; }
   __device__ __forceinline__ uint4 group(uint32_t slot) const { return *reinterpret_cast<const uint4*>(tab + slot); }
 };
-__device__ __forceinline__ bool group_has(const uint4& w, uint32_t id) {
-  return min(min(w.x ^ id, w.y ^ id), min(w.z ^ id, w.w ^ id)) == 0u;
+__device__ __forceinline__ uint64_t group_has(const uint4& w, uint32_t id) {  // lanes whose group holds their id
+  return ballot(min(min(w.x ^ id, w.y ^ id), min(w.z ^ id, w.w ^ id)) == 0u);
 }
-__device__ __forceinline__ bool group_full(const uint4& w) {  // no empty slot (ids are below kEmpty)
-  return max(max(w.x, w.y), max(w.z, w.w)) != kEmpty;
+__device__ __forceinline__ uint64_t group_full(const uint4& w) {  // no empty slot (ids are below kEmpty)
+  return ballot(max(max(w.x, w.y), max(w.z, w.w)) != kEmpty);
 }
 
 // Membership test.  For the LDS hash, end receives the slot where the probe
@@ -1099,6 +1109,7 @@ __device__ void search_one(const SearchArgs& a, int64_t q, uint8_t* lds, const q
   constexpr int DPL = BV::DPL;
   constexpr int LPN = BV::LPN;
   constexpr uint64_t kNone = ~0ull;  // sorts after every real entry
+  constexpr int64_t kBlock = qgl::block_bytes(D, R);
   const int lane = lane_id();
   int ef = a.ef, k = a.k;
   if constexpr (is_mixed<LS>) {
@@ -1172,7 +1183,7 @@ __device__ void search_one(const SearchArgs& a, int64_t q, uint8_t* lds, const q
   float de;
   {
     BV e;
-    e.load(a.blocks + (int64_t)a.entry * a.block_bytes, lane);
+    e.load(a.blocks + (int64_t)a.entry * kBlock, lane);
     de = uni(dist(e.x));
   }
   uint64_t tail = pack_kv(de, (uint32_t)a.entry);  // beam[ef - 1] whenever the beam is full
@@ -1273,7 +1284,7 @@ __device__ void search_one(const SearchArgs& a, int64_t q, uint8_t* lds, const q
     if (p == nxt_id)
       b = nxt;
     else
-      b.load(a.blocks + (int64_t)p * a.block_bytes, lane);
+      b.load(a.blocks + (int64_t)p * kBlock, lane);
     nxt_id = kEmpty;
     const float dp = uni(dist(b.x));
 
@@ -1344,7 +1355,7 @@ __device__ void search_one(const SearchArgs& a, int64_t q, uint8_t* lds, const q
     if (nxt_f != kNone) {
       const uint32_t nx = (uint32_t)nxt_f & kIdMask;
       if constexpr (BV::kRegPrefetch) {
-        nxt.load(a.blocks + (int64_t)nx * a.block_bytes, lane);
+        nxt.load(a.blocks + (int64_t)nx * kBlock, lane);
         nxt_id = nx;
       }
     }
@@ -1596,6 +1607,7 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
   constexpr int DPL = BV::DPL;
   constexpr int LPN = BV::LPN;
   constexpr uint64_t kNone = ~0ull;  // sorts after every real entry
+  constexpr int64_t kBlock = qgl::block_bytes(D, R);
   constexpr uint64_t kFlags = (uint64_t)(kChecked | kDup);
   const int lane = lane_id();
   int ef = a.ef, k = a.k;
@@ -1656,7 +1668,7 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
   // the entry starts the beam, keyed by its exact distance; it is the first
   // vertex expanded, so its block serves both
   BV b;
-  b.load(a.blocks + (int64_t)a.entry * a.block_bytes, lane);
+  b.load(a.blocks + (int64_t)a.entry * kBlock, lane);
   float dp = uni(dist(b.x));
   const float de = dp;
   uint32_t p = (uint32_t)a.entry;
@@ -1667,7 +1679,6 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
   for (int r = 0; r < NB; ++r) bw[r] = (r == 0 && lane == 0) ? pword : kNone;
   int size = 1;
   bool pending = false;  // a merge whose read-back has not been done yet
-  int pend_nv = 0;       // its number of candidates
   int nvis = 0, nnc = 0, expansions = 0, pops = 0, appended = 0, since = 0;
   float nn_wk = 0.0f;
   uint32_t nn_wi = 0;
@@ -1701,8 +1712,9 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
     const uint32_t pslot = vis.slot4(p);
     const uint32_t prun = vis.tab[(pslot + lane) & vis.mask];
     const uint32_t nb = (uint32_t)b.nb;
-    const bool probe = (lane % LPN == 0) && b.nb >= 0 && nb != p;
-    uint32_t ns = vis.slot4(probe ? nb : 0u);
+    constexpr uint64_t kFirstLanes = LPN == 2 ? 0x5555555555555555ull : ~0ull;  // one lane per neighbour
+    const uint64_t probe = kFirstLanes & ballot(b.nb >= 0) & ballot(nb != p);
+    uint32_t ns = vis.slot4(nb);  // of an empty slot's -1: some slot, not used
     uint4 ne = vis.group(ns);
     // FastScan estimates of all neighbours (Eq. normalization with Eq. 3.1)
     const int S = b.template fastscan<LB>(lut, lane, a.lut_pad, qsum);
@@ -1712,9 +1724,8 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
       int holes = 0;
 #pragma unroll
       for (int r = 0; r < NB; ++r) {
-        const bool hole = 64 * r + lane < size && bw[r] == kNone;
-        const uint64_t hm = ballot(hole);
-        if (hole) bw[r] = cbuf[holes + lanes_below(hm)];
+        const uint64_t hm = ballot(bw[r] == kNone) & mask_below(size - 64 * r);
+        if (lanes(hm)) bw[r] = cbuf[holes + lanes_below(hm)];
         holes += __popcll(hm);
       }
       if (size == ef) tail = rdlane64<NB>(bw, (ef - 1) >> 6, (ef - 1) & 63) & ~kFlags;
@@ -1727,7 +1738,7 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
     uint64_t um[NB], pm[NB];
 #pragma unroll
     for (int r = 0; r < NB; ++r) {
-      um[r] = ballot(!((uint32_t)bw[r] & kChecked));
+      um[r] = ballot((int32_t)(uint32_t)bw[r] >= 0);  // kChecked is the sign bit
       pm[r] = ballot(bw[r] == pword);
     }
     int rs = NB - 1, f = 0;
@@ -1743,7 +1754,7 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
       const uint64_t dup = r < rs ? um[r] : (r == rs ? (um[r] & before) : 0ull);
       pops += __popcll(dup);
       const uint64_t take = dup | (r == rs ? 1ull << f : 0ull);
-      if ((take >> lane) & 1ull) bw[r] |= kChecked;
+      if (lanes(take)) bw[r] |= kChecked;
     }
     ++pops;
     // p's other unchecked entries become consumed duplicates; the next
@@ -1756,9 +1767,9 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
 #pragma unroll
       for (int r = NB - 1; r >= 0; --r) {
         const uint32_t lo = (uint32_t)bw[r];
-        if ((lo & (kChecked | kDup | kIdMask30)) == p) bw[r] |= kDup;
-        const uint64_t fr_ = ballot(!((uint32_t)bw[r] & (kChecked | kDup)));
-        const uint64_t ur_ = ballot(!((uint32_t)bw[r] & kChecked));
+        if (lo == p) bw[r] |= kDup;  // no flag is set
+        const uint64_t fr_ = ballot((uint32_t)bw[r] < kDup);  // neither flag
+        const uint64_t ur_ = has_stop<LS> ? ballot((int32_t)(uint32_t)bw[r] >= 0) : 0ull;
         if (fr_) {
           rf = r;
           mf = fr_;
@@ -1776,7 +1787,7 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
     {
       uint64_t em = ballot(prun == kEmpty);
       if (em) {
-        if (lane == first_lane(em)) vis.tab[(pslot + lane) & vis.mask] = p;
+        if (lanes(em & (~em + 1))) vis.tab[(pslot + lane) & vis.mask] = p;
       } else {
         visited_add_absent(vis, p, pslot, lane);  // 64 occupied slots in a row (the table is at most half full)
       }
@@ -1792,37 +1803,39 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
 
     // visited filter: the probes that met four other ids go on to the next
     // group
-    bool seen = probe && group_has(ne, nb);
-    bool more = probe && !seen && group_full(ne);
-    while (ballot(more)) {
-      if (more) {
+    uint64_t seen = probe & group_has(ne, nb), more = probe & ~seen & group_full(ne);
+    while (more) {
+      uint64_t has = 0, full = 0;
+      if (lanes(more)) {
         ns = (ns + 4) & vis.mask;
         ne = vis.group(ns);
-        seen = group_has(ne, nb);
-        more = !seen && group_full(ne);
       }
+      has = group_has(ne, nb);
+      full = group_full(ne);
+      seen |= more & has;
+      more &= ~has & full;
     }
-    bool valid = probe && !seen;
-    const int app = uni((int)__popcll(ballot(valid)));
+    uint64_t V = probe & ~seen;
+    const int app = (int)__popcll(V);
     appended += app;
-    if (size == ef) valid = valid && cand < tail;  // would fall past the cut anyway
-    const uint64_t V = ballot(valid);
-    const int nv = uni((int)__popcll(V));
-    if (nv > 0 && valid) cbuf[lanes_below(V)] = cand;  // compacted for the merge's broadcast reads (after
-                                                         // the read-back above: LDS keeps order)
+    if (size == ef) V &= ballot(cand < tail);  // the others would fall past the cut anyway
+    const int nv = (int)__popcll(V);
+    const bool valid = lanes(V);
+    if (valid) cbuf[lanes_below(V)] = cand;  // compacted for the merge's broadcast reads (after the read-back
+                                             // above: LDS keeps order)
 
     // best candidate (the smallest (estimate, id) among them)
     uint64_t best = kNone;
     if (nv > 0) {
       const uint32_t hk = wave_min_u32(valid ? (uint32_t)(cand >> 32) : 0xFFFFFFFFu);
-      const uint64_t tie = ballot(valid && (uint32_t)(cand >> 32) == hk);
-      const uint32_t lo = (tie & (tie - 1)) ? wave_min_u32((tie >> lane) & 1 ? (uint32_t)cand : 0xFFFFFFFFu)
+      const uint64_t tie = V & ballot((uint32_t)(cand >> 32) == hk);
+      const uint32_t lo = (tie & (tie - 1)) ? wave_min_u32(lanes(tie) ? (uint32_t)cand : 0xFFFFFFFFu)
                                             : rdlane((uint32_t)cand, first_lane(tie));
       best = ((uint64_t)hk << 32) | lo;
     }
     // the next vertex to expand: prefetch its block (Sec. 3.1.4)
     const uint64_t nxt_f = best < o2f ? best : o2f;
-    if (nxt_f != kNone) nxt.load(a.blocks + (int64_t)((uint32_t)nxt_f & kIdMask30) * a.block_bytes, lane);
+    if (nxt_f != kNone) nxt.load(a.blocks + (int64_t)((uint32_t)nxt_f & kIdMask30) * kBlock, lane);
     const uint64_t nxt_u = best < o2u ? best : o2u;
     const float bfk = nxt_u == kNone ? __builtin_inff() : unsortable((uint32_t)(nxt_u >> 32));
 
@@ -1833,7 +1846,9 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
       if (nn_in_regs) {
         int pos = 0;
 #pragma unroll
-        for (int r = 0; r < NK; ++r) pos += (int)__popcll(ballot(64 * r + lane < nnc && kv_less(nrk[r], nri[r], dp, p)));
+        for (int r = 0; r < NK; ++r)
+          pos += (int)__popcll(mask_below(nnc - 64 * r) &
+                               (ballot(nrk[r] < dp) | (ballot(nrk[r] == dp) & ballot(nri[r] < p))));
         const int last = nnc < k ? nnc : k - 1;
 #pragma unroll
         for (int r = NK - 1; r >= 0; --r) {
@@ -1844,15 +1859,11 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
           const float upk =
               __int_as_float(__builtin_amdgcn_update_dpp(ck, __float_as_int(nrk[r]), 0x138, 0xF, 0xF, false));
           const uint32_t upi = (uint32_t)__builtin_amdgcn_update_dpp(ci, (int)nri[r], 0x138, 0xF, 0xF, false);
-          const int e = 64 * r + lane;
-          if (e > pos && e <= last) {
-            nrk[r] = upk;
-            nri[r] = upi;
-          }
-          if (e == pos) {
-            nrk[r] = dp;
-            nri[r] = p;
-          }
+          const uint64_t upto = mask_below(pos + 1 - 64 * r);
+          const bool move = lanes(mask_below(last + 1 - 64 * r) & ~upto);  // entries pos + 1 .. last
+          const bool put = lanes(upto & ~mask_below(pos - 64 * r));        // entry pos
+          nrk[r] = put ? dp : move ? upk : nrk[r];
+          nri[r] = put ? p : move ? upi : nri[r];
         }
         nnc = nnc < k ? nnc + 1 : k;
         if (nnc == k) {
@@ -1931,15 +1942,14 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
       const int nsz = (size + nv < ef) ? size + nv : ef;
 #pragma unroll
       for (int r = 0; r < NB; ++r)
-        if (64 * r + lane < nsz) sc[64 * r + lane] = kNone;
+        if (lanes(mask_below(nsz - 64 * r))) sc[64 * r + lane] = kNone;
 #pragma unroll
       for (int r = 0; r < NB; ++r) {
         const int np = 64 * r + lane + cnt[r];
-        if (64 * r + lane < size && np < ef) sc[np] = bw[r];
+        if (lanes(mask_below(size - 64 * r) & ballot(np < ef))) sc[np] = bw[r];
       }
       if (valid) cbuf[rank] = cand;  // after the count loop's reads (LDS keeps order)
       size = nsz;
-      pend_nv = nv;
     }
 
     if constexpr (has_stop<LS>) {
@@ -1962,7 +1972,7 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
       // no unconsumed entry is left (and no candidate, so no merge): every
       // remaining unchecked entry is a consumed duplicate, popped in turn
 #pragma unroll
-      for (int r = 0; r < NB; ++r) pops += __popcll(ballot(!((uint32_t)bw[r] & kChecked)));
+      for (int r = 0; r < NB; ++r) pops += __popcll(ballot((int32_t)(uint32_t)bw[r] >= 0));
       break;
     }
     p = (uint32_t)nxt_f & kIdMask30;
@@ -1970,7 +1980,6 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
     b = nxt;
     dp = uni(dist(b.x));
   }
-  (void)pend_nv;
 
   // answer: NN ascending by (distance, id), padded with (-1, inf)
   const int k_out = is_mixed<LS> ? a.k_out : k;
