@@ -210,15 +210,24 @@ __device__ __forceinline__ float exact_dist(const float (&qv)[DPL], const float 
 // round robin, so the T column blocks of one row block run on one XCD and read
 // those rows through its L2 once.  Workgroup 0 also clears `nzero` ints at
 // `zero` for the kernels that follow.  V4: the input rows start 16-byte
-// aligned, so each lane moves four columns per load and per LDS store.
-template <bool V4, int NT>
+// aligned, so each lane moves four columns per load and per LDS store.  KC
+// columns are staged at a time.
+//
+// Bound by the fp64 matrix cores (78.6 TFLOP/s; a large library product reaches
+// 63.6 here): 20,011 x 960 in 583 us (63.2 TFLOP/s), 10,000 x 768 in 202 us.
+// With 64 columns a chunk, twice the LDS and staging registers left 2-3
+// wavefronts on a SIMD and these took 642 and 230 us.
+template <bool V4, int NT, int KC>
 __global__ __launch_bounds__(64) void rotate_kernel(const float* __restrict__ in, int64_t n, int D,
                                                     const float* __restrict__ M, float* __restrict__ out,
                                                     int* __restrict__ zero, int nzero) {
-  // the block's 16 NT input rows and 16 NT rows of M, 64 columns at a time,
-  // staged through LDS with coalesced loads (rows padded to 68 floats); the
+  // the block's 16 NT input rows and 16 NT rows of M, KC columns at a time,
+  // staged through LDS with coalesced loads (rows padded by four floats); the
   // next chunk's loads are issued before this chunk's products
-  constexpr int KC = 64, LD = KC + 4, RB = 16 * NT;
+  constexpr int LD = KC + 4, RB = 16 * NT;
+  constexpr int VW = V4 ? 4 : 1, LR = KC / VW;  // columns a lane moves, lanes on a row
+  constexpr int RS = 64 / LR, NS = RB / RS;     // rows a step, steps
+  static_assert(LR * RS == 64 && NS * RS == RB, "whole rows and steps");
   __shared__ __align__(16) float As[RB * LD];
   __shared__ __align__(16) float Bs[RB * LD];
   const int lane = threadIdx.x;
@@ -234,48 +243,41 @@ __global__ __launch_bounds__(64) void rotate_kernel(const float* __restrict__ in
   for (int m = 0; m < NT; ++m)
 #pragma unroll
     for (int j = 0; j < NT; ++j) acc[m][j] = v4d{0.0, 0.0, 0.0, 0.0};
-  // V4: lane l moves columns 4 (l % 16) .. + 3 of rows l / 16 + 4 t; otherwise
-  // column l of every row.  Columns past kw (a multiple of 16) re-read the
-  // last valid ones into the unread part of the row.
-  float va[RB], vb[RB];
+  // columns past kw (a multiple of 16) re-read the last valid ones into the
+  // unread part of the row
+  float va[VW * NS], vb[VW * NS];
+  const int lc = VW * (lane % LR), lr = lane / LR;
   auto load = [&](int k0) __attribute__((always_inline)) {
     const int kw = D - k0 < KC ? D - k0 : KC;
-    if constexpr (V4) {
-      const int c = min(4 * (lane & 15), kw - 4);
+    const int c = min(lc, kw - VW);
 #pragma unroll
-      for (int t = 0; t < RB / 4; ++t) {
-        const int r = 4 * t + (lane >> 4);
-        const int64_t ra = r0 + r < n ? r0 + r : 0;  // rows past n only feed outputs that are not stored
-        const float4 x = *reinterpret_cast<const float4*>(in + ra * D + k0 + c);
-        const float4 y = *reinterpret_cast<const float4*>(M + (int64_t)(i0 + r) * D + k0 + c);
-        va[4 * t] = x.x, va[4 * t + 1] = x.y, va[4 * t + 2] = x.z, va[4 * t + 3] = x.w;
-        vb[4 * t] = y.x, vb[4 * t + 1] = y.y, vb[4 * t + 2] = y.z, vb[4 * t + 3] = y.w;
-      }
-    } else {
-      const int c = min(lane, kw - 1);
-#pragma unroll
-      for (int r = 0; r < RB; ++r) {
-        const int64_t ra = r0 + r < n ? r0 + r : 0;
-        va[r] = in[ra * D + k0 + c];
-        vb[r] = M[(int64_t)(i0 + r) * D + k0 + c];
+    for (int t = 0; t < NS; ++t) {
+      const int r = RS * t + lr;
+      const int64_t ra = r0 + r < n ? r0 + r : 0;  // rows past n only feed outputs that are not stored
+      const float* x = in + ra * D + k0 + c;
+      const float* y = M + (int64_t)(i0 + r) * D + k0 + c;
+      if constexpr (V4) {
+        const float4 xv = *reinterpret_cast<const float4*>(x), yv = *reinterpret_cast<const float4*>(y);
+        va[4 * t] = xv.x, va[4 * t + 1] = xv.y, va[4 * t + 2] = xv.z, va[4 * t + 3] = xv.w;
+        vb[4 * t] = yv.x, vb[4 * t + 1] = yv.y, vb[4 * t + 2] = yv.z, vb[4 * t + 3] = yv.w;
+      } else {
+        va[t] = *x;
+        vb[t] = *y;
       }
     }
   };
   load(0);
   for (int k0 = 0; k0 < D; k0 += KC) {
     const int kw = D - k0 < KC ? D - k0 : KC;
-    if constexpr (V4) {
 #pragma unroll
-      for (int t = 0; t < RB / 4; ++t) {
-        const int o = (4 * t + (lane >> 4)) * LD + 4 * (lane & 15);
+    for (int t = 0; t < NS; ++t) {
+      const int o = (RS * t + lr) * LD + lc;
+      if constexpr (V4) {
         *reinterpret_cast<float4*>(&As[o]) = make_float4(va[4 * t], va[4 * t + 1], va[4 * t + 2], va[4 * t + 3]);
         *reinterpret_cast<float4*>(&Bs[o]) = make_float4(vb[4 * t], vb[4 * t + 1], vb[4 * t + 2], vb[4 * t + 3]);
-      }
-    } else {
-#pragma unroll
-      for (int r = 0; r < RB; ++r) {
-        As[r * LD + lane] = va[r];
-        Bs[r * LD + lane] = vb[r];
+      } else {
+        As[o] = va[t];
+        Bs[o] = vb[t];
       }
     }
     __syncthreads();
@@ -2235,23 +2237,34 @@ hipError_t launch_rotate(const float* in, int64_t n, int D, const float* M, floa
                          hipStream_t st) {
   if (n <= 0) {
     if (zero && nzero > 0)
-      hipLaunchKernelGGL((rotate_kernel<false, 1>), dim3(1), dim3(64), 0, st, in, 0, D, M, out, zero, nzero);
+      hipLaunchKernelGGL((rotate_kernel<false, 1, 64>), dim3(1), dim3(64), 0, st, in, 0, D, M, out, zero, nzero);
     return hipGetLastError();
   }
   // four columns per lane when every row starts 16-byte aligned (M is the
-  // library's own allocation); 2 x 2 tiles per wavefront for the wide shapes
-  // (D = 768: 5-9% faster; D = 128: 3% slower at 10,000 rows, with a quarter
-  // as many wavefronts)
+  // library's own allocation)
   const bool v4 = (reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(M)) % 16 == 0 && D % 4 == 0;
-  const int nt = v4 && D % 32 == 0 && D > 256 ? 2 : 1;
+  // One tile a wavefront or a block of 2 x 2.  The block reads half as much per
+  // product, so a tile by itself costs about 1.2 times a quarter of it; but
+  // there are a quarter as many blocks to spread over the 1,024 SIMDs.  Rounds
+  // of products over the SIMDs, so weighed, decide as measured (one tile / 2 x
+  // 2): 37 x 960 18 / 40 us, 1,000 x 768 35 / 38, 1,000 x 960 51 / 47, 10,000 x
+  // 128 13.6 / 15.1, 20,011 x 128 21.7 / 20.5, 10,000 x 768 238 / 202.
+  auto rounds = [](int64_t tiles) { return (tiles + 1023) / 1024; };
+  const int64_t t1 = (n + 15) / 16 * (D / 16), t2 = (n + 31) / 32 * (D / 32);
+  const bool two = v4 && D % 32 == 0 && 4.0 * (double)rounds(t2) <= 1.2 * (double)rounds(t1);
+  const int nt = two ? 2 : 1;
   const int64_t blocks = (n + 16 * nt - 1) / (16 * nt);  // row blocks, padded to a multiple of 8 (one per XCD)
   const dim3 grid((unsigned)(((blocks + 7) / 8) * 8 * (D / (16 * nt))));
-  if (nt == 2)
-    hipLaunchKernelGGL((rotate_kernel<true, 2>), grid, dim3(64), 0, st, in, n, D, M, out, zero, nzero);
+  // 32 columns a chunk, or 64 where one-tile wavefronts are few and a chunk's
+  // loads take longer than its products (37 x 960: 18.1 against 19.9 us)
+  if (two)
+    hipLaunchKernelGGL((rotate_kernel<true, 2, 32>), grid, dim3(64), 0, st, in, n, D, M, out, zero, nzero);
+  else if (v4 && D > 256)
+    hipLaunchKernelGGL((rotate_kernel<true, 1, 64>), grid, dim3(64), 0, st, in, n, D, M, out, zero, nzero);
   else if (v4)
-    hipLaunchKernelGGL((rotate_kernel<true, 1>), grid, dim3(64), 0, st, in, n, D, M, out, zero, nzero);
+    hipLaunchKernelGGL((rotate_kernel<true, 1, 32>), grid, dim3(64), 0, st, in, n, D, M, out, zero, nzero);
   else
-    hipLaunchKernelGGL((rotate_kernel<false, 1>), grid, dim3(64), 0, st, in, n, D, M, out, zero, nzero);
+    hipLaunchKernelGGL((rotate_kernel<false, 1, 64>), grid, dim3(64), 0, st, in, n, D, M, out, zero, nzero);
   return hipGetLastError();
 }
 
