@@ -49,7 +49,7 @@ enum {
                               (plain search only: QG_EUNSUPPORTED with per-query k and ef or the learned stop) */
   QG_SEARCH_SMALL_HASH = 2, /* test hook: shrink the on-chip visited set to 128 slots so that queries take the
                               overflow path (results are identical by construction) */
-  QG_SEARCH_LDS_BEAM = 4    /* keep the beam in LDS for this call, as for beams above 256 entries, instead of in
+  QG_SEARCH_LDS_BEAM = 4    /* keep the beam in LDS for this call, as for beams above 512 entries, instead of in
                               registers (results are identical by construction) */
 };
 
@@ -220,7 +220,7 @@ int qg_set_stream(qg_index *idx, void *hip_stream);
  * pass), then, for the fastest pair, caps of 24, 20 and 16 resident
  * wavefronts per compute unit against no cap (a batch only a little larger
  * than the resident query slots can finish sooner on fewer, less contended
- * slots), then, for beams of at most 256 entries, the beam kept in LDS
+ * slots), then, where the beam is kept in registers, the beam kept in LDS
  * against the beam kept in registers, then the LUT layout (the per-query
  * table of Sec. 2.2's FastScan, rows of 16 entries: int16 or int32 entries,
  * with a padding row between the lane groups that share a neighbour, so that
@@ -254,7 +254,8 @@ int qg_autotune_mixed(qg_index *idx, const float *queries, int64_t nq, const int
 /* Set the launch shape directly (as qg_autotune would): wavefronts per
  * workgroup (1, 2, 4 or 8), visited-hash factor F (2, 3 or 4), the cap on
  * resident wavefronts per compute unit (0 = none, at most 64), the beam
- * storage (1: in registers for beams of at most 256 entries, the default;
+ * storage (1: in registers for beams of at most 256 entries, and of at most 512
+ * where that is faster, the default;
  * 0: always in LDS) and the LUT layout (0..3; bit 0: padded rows, bit 1:
  * int32 entries; 1, padded int16 rows, is the default).  Results do not
  * depend on it.  QG_EINVAL for values outside these sets. */

@@ -84,7 +84,7 @@ struct qg_index {
   int hash_factor = 3;
   int cu_waves = 0;  // cap on resident wavefronts per compute unit (0 = as many as fit)
   int cus = 256;     // compute units of the device (read at creation; sizes the persistent grid)
-  bool beam_regs = true;  // beams of at most 256 entries live in registers (else in LDS)
+  bool beam_regs = true;  // beams live in registers where that pays (else in LDS)
   bool lut_pad = true;    // LUT layout: a padding row between lane groups (else packed rows)
   bool lut32 = false;     // LUT entries int32 (else int16), for the plain and mixed main pass
   // timing
@@ -564,7 +564,7 @@ static int search_impl(const qg_index* cidx, const float* queries, int64_t nq, i
   // modes (the overflow pass and the other modes keep int16; shapes that sum
   // over bit planes have no table)
   const int lb = (idx->lut32 && (ls == 0 || ls == 3) && !qgl::use_planes(idx->D, idx->R)) ? 4 : 2;
-  const int nb = (idx->beam_regs && !(flags & QG_SEARCH_LDS_BEAM)) ? qgk::beam_regs(false, ls, ef, idx->N) : 0;
+  const int nb = (idx->beam_regs && !(flags & QG_SEARCH_LDS_BEAM)) ? qgk::beam_regs(false, ls, ef, idx->N, idx->D, nq) : 0;
   // NN needs LDS only where it outgrows its registers
   const int k_cap = k <= 64 * qgk::nn_regs(nb) ? 0 : k_cap_all;
   const int k_cap_ov = k <= 64 * qgk::nn_regs(0) ? 0 : k_cap_all;
@@ -709,7 +709,7 @@ static int autotune_impl(qg_index* idx, int64_t nq, int32_t kcap, int32_t ef_bou
       }
     }
   }
-  if (!rc && qgk::beam_regs(false, mixed ? 3 : 0, ef_bound, idx->N) > 0) {
+  if (!rc && qgk::beam_regs(false, mixed ? 3 : 0, ef_bound, idx->N, idx->D, nq) > 0) {
     idx->cu_waves = best_cw;  // the beam in LDS for the best shape
     idx->beam_regs = false;
     double t;

@@ -70,9 +70,10 @@ hipError_t launch_encode(const float* X, const float* ROT, int64_t N, int D, con
 // 3 per-query k and ef (k_q, ef_q set), 4 per-query k and ef with the learned
 // stop (MLP staged in LDS, as for 1), 5 "w/o ME" (the hash holds estimated
 // vertices, not visited ones)
-// nb: beam registers per lane (0: beam in LDS; 1 .. 4: ef up to 64 nb), as
-// beam_regs() picks for the pass, mode, bound on ef and vector count.
-int beam_regs(bool overflow_pass, int ls_mode, int ef_bound, int64_t n);
+// nb: beam registers per lane (0: beam in LDS; 1 .. 4, 6, 8: ef up to 64 nb), as
+// beam_regs() picks for the pass, mode, bound on ef, vector count, dimension
+// and batch size.
+int beam_regs(bool overflow_pass, int ls_mode, int ef_bound, int64_t n, int D, int64_t nq);
 // NN registers per lane of a kernel with nb beam registers (nb 0: beam in LDS);
 // larger k keep NN in LDS
 constexpr int nn_regs(int nb) { return nb >= 3 ? nb : 1; }

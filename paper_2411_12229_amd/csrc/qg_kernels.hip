@@ -1854,6 +1854,7 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
         const int last = nnc < k ? nnc : k - 1;
 #pragma unroll
         for (int r = NK - 1; r >= 0; --r) {
+          if (r > 0 && 64 * r > last) continue;  // holds none
           // the entries before, one lane up (DPP shift of the wavefront by one
           // lane; lane 0 takes lane 63 of the register below)
           const int ck = r > 0 ? __float_as_int(rdlane(nrk[r > 0 ? r - 1 : 0], 63)) : 0;
@@ -2015,7 +2016,7 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
 
 // Minimum wavefronts per SIMD the register allocator must allow (1: no
 // constraint).  Beams of three and four registers at D <= 256: 4 (LDS allows
-// hardly more; at 6 they spill 100-190 bytes).  LDS-beam kernels with D <= 256: 6 for the stop-only and
+// hardly more; at 6 they spill 100-190 bytes); of six and eight: 3.  LDS-beam kernels with D <= 256: 6 for the stop-only and
 // mixed-batch modes.  Register-beam kernels with R = 32, plain or mixed
 // batches, D = 128 (but the one-word plain kernel, which fits in 80 registers
 // anyway) and D = 96: 6, where the allocator would otherwise take 82-96
@@ -2027,6 +2028,7 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
 // bytes of scratch, 1-2% slower); R = 64 would spill over 100 bytes.
 template <int D, int R, int LS, int NB>
 constexpr int waves_hint() {
+  if constexpr (NB > 4) return D <= 256 ? 3 : 1;
   if constexpr (NB > 2) return D <= 256 ? 4 : 1;
   if constexpr (NB > 0) {
     constexpr bool mode = LS == kLsOff || LS == kMixed;
@@ -2152,7 +2154,9 @@ static Ret dispatch_mode(bool gv, int ls, int nb, int lb, const Op& op, Ret bad)
   (nb == 1   ? op.template run<D, R, false, ls_, 1, lb_>()                                      \
    : nb == 2 ? op.template run<D, R, false, ls_, 2, lb_>()                                      \
    : nb == 3 ? op.template run<D, R, false, ls_, 3, lb_>()                                      \
-   : nb == 4 ? op.template run<D, R, false, ls_, 4, lb_>() : op.template run<D, R, false, ls_, 0, lb_>())
+   : nb == 4 ? op.template run<D, R, false, ls_, 4, lb_>()                                      \
+   : nb == 6 ? op.template run<D, R, false, ls_, 6, lb_>()                                      \
+   : nb == 8 ? op.template run<D, R, false, ls_, 8, lb_>() : op.template run<D, R, false, ls_, 0, lb_>())
   if (lb == 4) {
     if constexpr (qgl::use_planes(D, R)) return bad;
     else switch (ls) {
@@ -2290,12 +2294,20 @@ hipError_t launch_encode(const float* X, const float* ROT, int64_t N, int D, con
 // one query, 538 against 660 us for 3,001 queries, 1,251 against 1,376 us for
 // 10,000; four (ef 250) 413 against 518, 778 against 893 and 1,767 against
 // 1,845 us.  The LDS merge's binary searches are a chain of dependent reads,
-// the register merge one pass over the candidates.
-int beam_regs(bool overflow_pass, int ls_mode, int ef_bound, int64_t n) {
+// the register merge one pass over the candidates.  Six and eight registers
+// (ef up to 384 and 512) always for the wide shapes (960 x 64: 1,000 queries at
+// ef 384 1,504 against 1,026 us, 10,000 7,073 against 5,258), and for the
+// narrow ones while the batch is resident at once, at three wavefronts a SIMD:
+// there 96 x 32 takes 1,241 against 828 us at ef 384 and 1,000 queries, but
+// 128 x 32 at ef 512 and 10,000 queries 3,314 against 3,652, for the LDS beam
+// fits five wavefronts.
+int beam_regs(bool overflow_pass, int ls_mode, int ef_bound, int64_t n, int D, int64_t nq) {
   if (overflow_pass || ls_mode == kLsTrace || ls_mode == kNoMe || n > (int64_t)kIdMask30) return 0;
   if (ef_bound <= 64) return 1;
   if (ls_mode != kLsOff && ls_mode != kMixed) return 0;
-  return ef_bound <= 256 ? (ef_bound + 63) / 64 : 0;
+  if (ef_bound <= 256) return (ef_bound + 63) / 64;
+  if (ef_bound > 512 || (D <= 256 && nq > 3 * 1024)) return 0;
+  return ef_bound <= 384 ? 6 : 8;
 }
 
 #define QG_DIMS(X) X(96) X(128) X(768) X(960)

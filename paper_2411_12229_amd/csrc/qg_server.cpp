@@ -153,15 +153,15 @@ void free_slot(Slot& s) {
 
 // One batch of a single zero query through every step a batch takes
 // (uploads, search, downloads, events) for each beam storage a batch can get
-// (a beam of one entry, of 65, 129, 193 and 257: one to four register words
-// per lane, or LDS), with the stop if `stop` is given, so that every kernel a batch may
+// (beams of one entry, of 65, 129, 193, 257, 385 and 513: one to four, six or
+// eight register words per lane, or LDS), with the stop if `stop` is given, so that every kernel a batch may
 // launch is loaded, and the copy paths set up, before the first request: the
 // first launch of a kernel loads its code and takes milliseconds.
 bool warm_up(qg_server* sv, Slot& s, const qg_stop_params* stop) {
   const size_t K = (size_t)sv->k_max, D = (size_t)sv->D;
   std::memset(s.h_q, 0, sizeof(float) * D);
   s.h_k[0] = 1;
-  for (int32_t ef : {1, 65, 129, 193, 257}) {
+  for (int32_t ef : {1, 65, 129, 193, 257, 385, 513}) {
     if (ef > sv->ef_max) break;
     s.h_ef[0] = ef;
     const bool ok =

@@ -42,7 +42,7 @@ def made():
 @pytest.mark.parametrize("D,R", [(96, 32), (128, 64), (960, 64)])
 @pytest.mark.parametrize("k,ef", [
     (10, 64), (10, 65), (65, 128), (128, 129), (129, 192), (192, 193), (193, 256), (256, 256), (257, 256),
-    (300, 193), (10, 257), (64, 130), (1, 255),
+    (300, 193), (10, 257), (64, 130), (1, 255), (384, 384), (385, 384), (10, 385), (100, 512), (513, 512), (10, 513),
 ])
 def test_equals_oracle(made, D, R, k, ef):
     idx, blocks, M, e, Q = made(D, R)
@@ -55,7 +55,7 @@ def test_equals_oracle(made, D, R, k, ef):
 
 
 @pytest.mark.parametrize("D,R", [(96, 32), (960, 64)])
-@pytest.mark.parametrize("k_max,ef_max", [(300, 200), (100, 192), (260, 256)])
+@pytest.mark.parametrize("k_max,ef_max", [(300, 200), (100, 192), (260, 256), (400, 300), (100, 500)])
 def test_mixed_rows_equal_oracle(made, D, R, k_max, ef_max):
     """Per-query settings over the whole range of one launch, output rows wider than the registers hold."""
     idx, blocks, M, e, Q = made(D, R)
