@@ -60,7 +60,6 @@ constexpr int kPruneThreads = 64 * kPruneWaves;
 // for D <= 1024.  Sum 1.11e-3.
 constexpr float kCosErr = 1.25e-3f;
 constexpr float kUnitScale = 4096.0f;                        // f16 elements hold 2^12 times the unit vector's
-constexpr float kDotScale = 1.0f / (kUnitScale * kUnitScale);
 
 // Dynamic LDS of prune_kernel (bytes).  stage: the f16 rows of one chunk of KC
 // dimensions, and before that the sort; occ: row w's bits over the 32-blocks
@@ -91,6 +90,7 @@ __host__ __device__ inline PruneLds prune_lds(int C, int R, int KC) {
 }
 
 __device__ __forceinline__ void wave_sync() { __builtin_amdgcn_wave_barrier(); }
+__device__ __forceinline__ bool lanes(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 
 // Doubles as integers of the same order (cosines; no NaN is ever stored).
 __device__ __forceinline__ unsigned long long sortable64(double x) {
@@ -107,7 +107,7 @@ __device__ __forceinline__ float unsortable32(int s) { return __int_as_float(s <
 __device__ __forceinline__ double dot_seq(const float* __restrict__ xw, const float* __restrict__ xv,
                                           const float* __restrict__ xu, int D) {
   double s = 0.0;
-#pragma unroll 2
+#pragma unroll 8
   for (int t = 0; t < D; t += 4) {
     const float4 w4 = *reinterpret_cast<const float4*>(xw + t);
     const float4 v4 = *reinterpret_cast<const float4*>(xv + t);
@@ -154,9 +154,13 @@ __device__ __forceinline__ double dot_seq(const float* __restrict__ xw, const fl
 // Computing every tested pair in fp64 by one lane each is what bound the
 // pruning before: 50,000 x 128 at 232 candidates took 123 ms for the
 // refinement, 4.4 ms per NSG pass and 2.9 ms for the candidate lists, and
-// takes 6.5 ms per iteration now, refinement included; 6,001 x 960 at 214
-// candidates 287, 8.6 and 1.5 ms, now 4.8 ms.  What bounds it now is latency:
-// the rows' loads and the one or two rounds of exact sums per vertex.
+// takes 5.3 ms per iteration now, refinement included; 6,001 x 960 at 214
+// candidates 287, 8.6 and 1.5 ms, now 4.45 ms.  What bounds it now: at 960
+// dimensions the rows' bytes (about 5 MB a vertex with the exact sums, 6 TB/s
+// through L2 and the last-level cache); at 128 latency, two workgroups a
+// compute unit, of 129,000 cycles each 30,000 for the products with their
+// loads, 28,000 for the exact sums, 18,000 for the comparisons, 15,000 for the
+// distances, 12,000 for the order.
 // T: 32 x 32 tiles of cosines a wavefront holds in one pass over the
 // dimensions (16 registers each).
 struct PruneArgs {
@@ -199,6 +203,7 @@ __global__ __launch_bounds__(kPruneThreads, T <= 5 ? 4 : 2) void prune_kernel(Pr
   while (P < C) P <<= 1;
   unsigned long long* sk = reinterpret_cast<unsigned long long*>(sm + L.stage);  // P sort keys: distance bits
   int32_t* si = reinterpret_cast<int32_t*>(sk + P);                               // P ids
+  int nres;  // search results among the candidates (the first ones)
   if (wave == 0) {
     const int32_t* srow = a.sids + (int64_t)blockIdx.x * a.EF;
     int n = 0;
@@ -216,10 +221,11 @@ __global__ __launch_bounds__(kPruneThreads, T <= 5 ? 4 : 2) void prune_kernel(Pr
   {
     // a neighbour list holds no id twice, so each is compared with the results
     // alone; the order of appending does not matter (the list is sorted next)
-    const int nres = scal[0];
+    nres = __builtin_amdgcn_readfirstlane(scal[0]);
     __syncthreads();
+    const int32_t row = lane < R ? a.G[u * R + lane] : -1;  // R <= 64
     for (int j = wave; j < R; j += kPruneWaves) {
-      const int32_t v = a.G[u * R + j];
+      const int32_t v = __builtin_amdgcn_readlane(row, j);
       if (v < 0 || v == (int32_t)u) continue;
       bool dup = false;
       for (int i = lane; i < nres; i += 64) dup |= si[i] == v;
@@ -237,27 +243,73 @@ __global__ __launch_bounds__(kPruneThreads, T <= 5 ? 4 : 2) void prune_kernel(Pr
     sk[i] = k;  // a sum of squares: its bits order as the value does
   }
   __syncthreads();
-  // bitonic sort; with a distance of at most 64 between partners a wavefront's
-  // 128 elements are its own, so only the wider steps need the barrier
-  for (int k = 2; k <= P; k <<= 1)
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int t = tid; t < P / 2; t += kPruneThreads) {
-        const int i = ((t & ~(j - 1)) << 1) | (t & (j - 1)), l = i | j;
-        const bool up = (i & k) == 0;
-        const unsigned long long di = sk[i], dl = sk[l];
-        const int32_t ii = si[i], il = si[l];
-        if ((di > dl || (di == dl && ii > il)) == up) {
-          sk[i] = dl;
-          sk[l] = di;
-          si[i] = il;
-          si[l] = ii;
+  // The search results come ordered by their fp32 distances, which is nearly
+  // always the fp64 order too.  If it is, only the neighbours after them have
+  // to be merged in: everyone's place is its own number plus the others before
+  // it.  Otherwise the whole list is sorted.
+  auto before = [&](int i, int j) { return sk[i] < sk[j] || (sk[i] == sk[j] && si[i] < si[j]); };
+  bool ordered = true;
+  for (int i = tid; i + 1 < nres; i += kPruneThreads) ordered &= before(i, i + 1);
+  if (__syncthreads_and(ordered)) {
+    unsigned long long key[3];
+    int32_t who[3];
+    int place[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {  // n <= 1088
+      const int i = tid + c * kPruneThreads;
+      place[c] = -1;
+      if (i < n) {
+        key[c] = sk[i];
+        who[c] = si[i];
+        int pl = 0;
+        for (int j = nres; j < n; ++j) pl += before(j, i);
+        if (i < nres) {
+          pl += i;
+        } else {
+          int lo = 0, hi = nres;  // results [0, lo) precede it
+          while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (before(mid, i))
+              lo = mid + 1;
+            else
+              hi = mid;
+          }
+          pl += lo;
         }
+        place[c] = pl;
       }
-      if (j > 64 || (j == 1 && k >= 128))
-        __syncthreads();
-      else
-        wave_sync();
     }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      if (place[c] >= 0) {
+        sk[place[c]] = key[c];
+        si[place[c]] = who[c];
+      }
+  } else {
+    // bitonic sort; with a distance of at most 64 between partners a
+    // wavefront's 128 elements are its own, so only the wider steps need the
+    // barrier
+    for (int k = 2; k <= P; k <<= 1)
+      for (int j = k >> 1; j > 0; j >>= 1) {
+        for (int t = tid; t < P / 2; t += kPruneThreads) {
+          const int i = ((t & ~(j - 1)) << 1) | (t & (j - 1)), l = i | j;
+          const bool up = (i & k) == 0;
+          const unsigned long long di = sk[i], dl = sk[l];
+          const int32_t ii = si[i], il = si[l];
+          if ((di > dl || (di == dl && ii > il)) == up) {
+            sk[i] = dl;
+            sk[l] = di;
+            si[i] = il;
+            si[l] = ii;
+          }
+        }
+        if (j > 64 || (j == 1 && k >= 128))
+          __syncthreads();
+        else
+          wave_sync();
+      }
+  }
   __syncthreads();
   const int nt = (n + 31) / 32, nc = 32 * nt;
   const double smax = n > 0 ? __builtin_sqrt(__longlong_as_double((long long)sk[n - 1])) : 0.0;
@@ -270,7 +322,7 @@ __global__ __launch_bounds__(kPruneThreads, T <= 5 ? 4 : 2) void prune_kernel(Pr
     id[i] = live ? si[i] : 0;
     rw[i] = (float)r;
     hv[i] = live ? 0.5f / (float)r : 0.0f;
-    cmax[i] = sortable32(-2.0f);
+    cmax[i] = sortable32(-2.0f * kUnitScale * kUnitScale);
     tv[i] = sortable64(-2.0);
   }
 
@@ -285,7 +337,7 @@ __global__ __launch_bounds__(kPruneThreads, T <= 5 ? 4 : 2) void prune_kernel(Pr
     const float* xw = X + (int64_t)id[w] * D;
     const float* xv = X + (int64_t)id[v] * D;
     if (which == 0) {
-      if (dist2_seq<4>(xw, xv, D) < cd[v]) atomicOr(&occ[occ_row(w) + (v >> 5) - (w >> 5)], 1u << (v & 31));
+      if (dist2_seq<8>(xw, xv, D) < cd[v]) atomicOr(&occ[occ_row(w) + (v >> 5) - (w >> 5)], 1u << (v & 31));
     } else {
       const double nw = cd[w], nv = cd[v];
       const double cs = (nv > 0.0 && nw > 0.0) ? dot_seq(xw, xv, xu, D) / (__builtin_sqrt(nv) * __builtin_sqrt(nw))
@@ -335,7 +387,11 @@ __global__ __launch_bounds__(kPruneThreads, T <= 5 ? 4 : 2) void prune_kernel(Pr
   const int npairs = nt * (nt + 1) / 2;
   const int passes = (npairs + T * kPruneWaves - 1) / (T * kPruneWaves);
   const int per = passes ? (npairs + passes * kPruneWaves - 1) / (passes * kPruneWaves) : 0;  // tiles a wavefront holds
-  const int rowsh = KC == 32 ? 3 : 2;  // log2 of the lanes staging one row (four dimensions each)
+  const int rowsh = KC == 64 ? 4 : KC == 32 ? 3 : 2;  // log2 of the lanes staging one row (four dimensions each)
+  // place of a row's 16-byte slot s
+  auto slot_of = [&](int s, int r) {
+    return KC == 64 ? s ^ (r & 7) : KC == 32 ? s ^ ((r >> 1) & 3) : s ^ ((r >> 2) & 1);
+  };
   for (int pass = 0; pass < passes; ++pass) {
     const int p0 = (pass * kPruneWaves + wave) * per;
     const int mine = p0 >= npairs ? 0 : (npairs - p0 < per ? npairs - p0 : per);
@@ -373,14 +429,14 @@ __global__ __launch_bounds__(kPruneThreads, T <= 5 ? 4 : 2) void prune_kernel(Pr
           h.y = (_Float16)((float)(((double)x4.y - (double)u4.y) * ismax) * f);
           h.z = (_Float16)((float)(((double)x4.z - (double)u4.z) * ismax) * f);
           h.w = (_Float16)((float)(((double)x4.w - (double)u4.w) * ismax) * f);
-          const int slot = KC == 32 ? (c >> 3) ^ ((r >> 1) & 3) : (c >> 3) ^ ((r >> 2) & 1);
+          const int slot = slot_of(c >> 3, r);
           *reinterpret_cast<half4*>(stage + r * KC + slot * 8 + (c & 4)) = h;
         }
       }
       __syncthreads();
       for (int ks = 0; ks < KC; ks += 16) {
         const int s = (ks >> 3) + (lane >> 5), r = lane & 31;
-        const int slot = KC == 32 ? s ^ ((r >> 1) & 3) : s ^ ((r >> 2) & 1);
+        const int slot = slot_of(s, r);
         const _Float16* base = stage + r * KC + slot * 8;
 #pragma unroll
         for (int t = 0; t < T; ++t)
@@ -392,55 +448,75 @@ __global__ __launch_bounds__(kPruneThreads, T <= 5 ? 4 : 2) void prune_kernel(Pr
       }
     }
     // lane l holds column v = 32 J + l % 32, rows w = 32 I + 8 (i / 4) + 4 (l / 32) + i % 4
-    uint32_t mask[(T + 1) / 2];
+    // The comparisons are made on the products as they are, against limits
+    // scaled alike.  A pair whose |w - u| is lost beside |v - u|, or with a
+    // norm of zero or beyond fp32, is left open (the limits are not ordered
+    // for NaN); that is looked for once a tile, in its first row, which has the
+    // smallest |w - u|.
+    uint32_t mask[(T + 1) / 2], maskb[(T + 1) / 2];
 #pragma unroll
-    for (int t = 0; t < (T + 1) / 2; ++t) mask[t] = 0;
+    for (int t = 0; t < (T + 1) / 2; ++t) mask[t] = maskb[t] = 0;
 #pragma unroll
     for (int t = 0; t < T; ++t)
       if (t < mine) {
         const int I = tile[t] & 255, J = tile[t] >> 8, v = 32 * J + (lane & 31);
-        const float h = hv[v];
-        const int w0 = 32 * I + 4 * half, below = (v < n ? v : 0) - w0;  // rows w0 + o with o < below are pairs
-        float cm = -2.0f;
+        const float h = hv[v] * (kUnitScale * kUnitScale);
+        const int w0 = 32 * I + 4 * half;
+        const int below = (I == J ? v - w0 : 32) & (v < n ? -1 : 0);  // rows w0 + o with o < below are pairs
+        const bool plain = (ballot(rw[32 * I] * h < 1e-6f * kUnitScale * kUnitScale) & ballot(v < n)) == 0;
+        float cm = -2.0f * kUnitScale * kUnitScale;
         uint32_t open = 0;  // pairs the approximation leaves open
-        uint32_t* ow = occ + occ_row(w0) + J - I;  // word of row w0 + o: o rows of nt - I words on
+        uint32_t word = 0;  // lane i, 32 + i: the bits of this tile's register i
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-          const int o = 8 * (i >> 2) + (i & 3), w = w0 + o;
-          const bool pair = o < below;
-          const float cs = acc[t][i] * kDotScale, thr = rw[w] * h;
-          const bool can = thr >= 1e-6f;  // else |w - u| is lost beside |v - u|; false for a zero or huge norm (NaN)
-          const bool yes = can && cs > thr + kCosErr, no = can && cs < thr - kCosErr;
-          const uint64_t ym = ballot(pair && yes);
-          if ((lane & 31) == 0) ow[o * (nt - I)] = half ? (uint32_t)(ym >> 32) : (uint32_t)ym;
-          open |= pair && !yes && !no ? 1u << i : 0u;
-          cm = pair && can ? fmaxf(cm, cs) : cm;
-          asm volatile("" : "+v"(open), "+v"(cm));  // row by row: the rows' conditions would fill the scalar registers
+          const int o = 8 * (i >> 2) + (i & 3);
+          const float c = acc[t][i], r = rw[w0 + o];
+          const uint64_t pair = ballot(o < below);
+          uint64_t yes = ballot(c > __builtin_fmaf(r, h, kCosErr * kUnitScale * kUnitScale)) & pair;
+          uint64_t no = ballot(c < __builtin_fmaf(r, h, -kCosErr * kUnitScale * kUnitScale));
+          uint64_t can = ~0ull;
+          if (!plain) {
+            can = ballot(r * h >= 1e-6f * kUnitScale * kUnitScale);
+            yes &= can;
+            no &= can;
+          }
+          word = lanes(1ull << i) ? (uint32_t)yes : word;
+          word = lanes(1ull << (32 + i)) ? (uint32_t)(yes >> 32) : word;
+          open |= lanes(pair & ~yes & ~no) ? 1u << i : 0u;
+          if (a.refine) cm = lanes(pair & can) ? fmaxf(cm, c) : cm;
+          asm volatile("" : "+v"(open), "+v"(cm), "+v"(word));  // row by row
         }
+        const int wr = 32 * I + 8 * ((lane & 15) >> 2) + 4 * half + (lane & 3);
+        if ((lane & 31) < 16) occ[occ_row(wr) + J - I] = word;
         mask[t >> 1] |= open << (16 * (t & 1));
-        if (a.refine && cm > -2.0f) atomicMax(&cmax[v], sortable32(cm));
+        if (a.refine && below > 0) atomicMax(&cmax[v], sortable32(cm));
       }
-    drain(0, mask, tile);
     if (a.refine) {
       __syncthreads();  // every wavefront's column maxima of this pass
 #pragma unroll
       for (int t = 0; t < T; ++t)
         if (t < mine) {
           const int I = tile[t] & 255, J = tile[t] >> 8, v = 32 * J + (lane & 31);
-          const float h = hv[v], lim = unsortable32(cmax[v]) - 2.0f * kCosErr;
-          const int w0 = 32 * I + 4 * half, below = (v < n ? v : 0) - w0;
+          const float h = hv[v] * (kUnitScale * kUnitScale);
+          const float lim = unsortable32(cmax[v]) - 2.0f * kCosErr * kUnitScale * kUnitScale;
+          const int w0 = 32 * I + 4 * half;
+          const int below = (I == J ? v - w0 : 32) & (v < n ? -1 : 0);
+          const bool plain = (ballot(rw[32 * I] * h < 1e-6f * kUnitScale * kUnitScale) & ballot(v < n)) == 0;
           uint32_t open = 0;
 #pragma unroll
           for (int i = 0; i < 16; ++i) {
             const int o = 8 * (i >> 2) + (i & 3);
-            const bool out = rw[w0 + o] * h >= 1e-6f && acc[t][i] * kDotScale < lim;
-            open |= o < below && !out ? 1u << i : 0u;
+            uint64_t out = ballot(acc[t][i] < lim);
+            if (!plain) out &= ballot(rw[w0 + o] * h >= 1e-6f * kUnitScale * kUnitScale);
+            open |= lanes(ballot(o < below) & ~out) ? 1u << i : 0u;
             asm volatile("" : "+v"(open));
           }
-          mask[t >> 1] |= open << (16 * (t & 1));
+          maskb[t >> 1] |= open << (16 * (t & 1));
         }
-      drain(1, mask, tile);
     }
+    // the products are used up: their registers hold the rows of the exact sums
+    drain(0, mask, tile);
+    if (a.refine) drain(1, maskb, tile);
   }
   __syncthreads();
 
@@ -543,8 +619,11 @@ hipError_t launch_prune(const float* X, int D, const int32_t* sids, int EF, cons
   if (nu <= 0) return hipSuccess;
   const int C = EF + R;  // EF results and R old neighbours
   if (D % 32 || D > 1024 || R > 64 || C > 32 * 34) return hipErrorInvalidValue;
-  // chunks of 32 dimensions, or 16 where the lists are so long that the LDS asks for it
-  const int KC = prune_lds(C, R, 32).total <= 160 * 1024 ? 32 : 16;
+  // Chunks of 64 dimensions where they divide (half as many waits for the rows'
+  // loads as with 32; two workgroups of the five-tile kernel still fit a
+  // compute unit), fewer where the lists are so long that the LDS asks for it
+  int KC = D % 64 ? 32 : 64;
+  while (prune_lds(C, R, KC).total > 160 * 1024) KC >>= 1;
   const size_t lds = (size_t)prune_lds(C, R, KC).total;
   const PruneArgs a{X, N, sids, G, fill, Gout, u0, D, EF, R, C, KC, refine};
   // lists of up to 256 candidates are 36 tiles, 5 a wavefront: few enough
