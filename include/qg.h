@@ -107,7 +107,7 @@ enum {
  * -1 = empty slot) are device arrays; out_stats (host, nullable) receives
  * [vertices reachable before the repair, repairs made, reachable after,
  * elapsed microseconds].  Synchronous; allocates its working memory (about
- * 8 n r + 8 min(n, 65536) ef_build bytes beside an index). */
+ * 4 n d + 8 n r + 12 n + 8 min(n, 65536) ef_build bytes beside an index). */
 int qg_build_graph(const float *vectors, int64_t n, int32_t d, int32_t r, int32_t ef_build, int32_t iters,
                    const float *rotation, int32_t entry, const int32_t *init_graph, const int32_t *fill,
                    int32_t flags, int device, int32_t *out_graph, int64_t *out_stats);

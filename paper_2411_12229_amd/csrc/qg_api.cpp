@@ -214,6 +214,62 @@ qg_index* make_view(const qg_index* base) {
   return v;
 }
 
+int begin_index(const float* vectors, int64_t n, int32_t d, int32_t r, const float* rotation, int32_t entry,
+                int device, qg_index** out, float** rotated) {
+  *out = nullptr;
+  *rotated = nullptr;
+  int rc = validate_shape(n, d, r);
+  if (rc) return rc;
+  if (entry < 0 || entry >= n) return fail(QG_EINVAL, "entry out of range");
+  int ndev = 0;
+  HIP_TRY(hipGetDeviceCount(&ndev), "hipGetDeviceCount");
+  if (device < 0 || device >= ndev) return fail(QG_EINVAL, "bad device");
+  DeviceGuard g(device);
+  qg_index* idx = new qg_index;
+  idx->device = device;
+  idx->N = n;
+  idx->D = d;
+  idx->R = r;
+  idx->entry = entry;
+  idx->block_bytes = qgl::block_bytes(d, r);
+  if ((rc = alloc_common(idx)) != QG_OK) {
+    release(idx);
+    return rc;
+  }
+  float* tmp = nullptr;
+  hipError_t e = hipMalloc(&tmp, sizeof(float) * (size_t)(n * d));
+  if (e != hipSuccess) {
+    release(idx);
+    return hip_fail(e, "hipMalloc rotated vectors");
+  }
+  e = hipMemcpy(idx->rot, rotation, sizeof(float) * d * d, hipMemcpyDeviceToDevice);
+  if (e == hipSuccess) e = qgk::launch_rotate(vectors, n, d, idx->rot, tmp, nullptr, 0, nullptr);
+  if (e != hipSuccess) {
+    (void)hipFree(tmp);
+    release(idx);
+    return hip_fail(e, "rotate vectors");
+  }
+  *out = idx;
+  *rotated = tmp;
+  return QG_OK;
+}
+
+int encode_index(qg_index* idx, const float* vectors, const float* rotated, const int32_t* graph) {
+  DeviceGuard g(idx->device);
+  // every neighbour id becomes a block address in the kernels: the encoder
+  // checks them all (the last counter is its flag; searches clear the counters
+  // before they use them)
+  int bad = 0;
+  int* const flag = idx->counters + kCounters - 1;
+  HIP_TRY(hipMemsetAsync(flag, 0, sizeof bad, nullptr), "encode");
+  HIP_TRY(qgk::launch_encode(vectors, rotated, idx->N, idx->D, graph, idx->R, idx->blocks, idx->block_bytes, flag,
+                             nullptr),
+          "encode");
+  HIP_TRY(hipMemcpy(&bad, flag, sizeof bad, hipMemcpyDeviceToHost), "encode");  // waits for the encoder
+  if (bad) return fail(QG_EINVAL, bad & 1 ? "graph id out of range" : "a neighbour list repeats an id");
+  return QG_OK;
+}
+
 int set_error(int code, const std::string& msg) { return fail(code, msg); }
 int device_of(const qg_index* idx) { return idx->device; }
 int dim_of(const qg_index* idx) { return idx->D; }
@@ -265,48 +321,16 @@ int qg_build_index(const float* vectors, int64_t n, int32_t d, const int32_t* gr
   if (!out) return fail(QG_EINVAL, "out is NULL");
   *out = nullptr;
   if (!vectors || !graph || !rotation) return fail(QG_EINVAL, "NULL array");
-  int rc = validate_shape(n, d, r);
+  float* rotated = nullptr;
+  qg_index* idx = nullptr;
+  int rc = qgi::begin_index(vectors, n, d, r, rotation, entry, device, &idx, &rotated);
   if (rc) return rc;
-  if (entry < 0 || entry >= n) return fail(QG_EINVAL, "entry out of range");
-  int ndev = 0;
-  HIP_TRY(hipGetDeviceCount(&ndev), "hipGetDeviceCount");
-  if (device < 0 || device >= ndev) return fail(QG_EINVAL, "bad device");
+  rc = qgi::encode_index(idx, vectors, rotated, graph);
   DeviceGuard g(device);
-  qg_index* idx = new qg_index;
-  idx->device = device;
-  idx->N = n;
-  idx->D = d;
-  idx->R = r;
-  idx->entry = entry;
-  idx->block_bytes = qgl::block_bytes(d, r);
-  if ((rc = alloc_common(idx)) != QG_OK) {
+  (void)hipFree(rotated);
+  if (rc) {
     release(idx);
     return rc;
-  }
-  float* tmp = nullptr;
-  hipError_t e = hipMalloc(&tmp, sizeof(float) * (size_t)(n * d));
-  if (e != hipSuccess) {
-    release(idx);
-    return hip_fail(e, "hipMalloc rotated vectors");
-  }
-  e = hipMemcpy(idx->rot, rotation, sizeof(float) * d * d, hipMemcpyDeviceToDevice);
-  // every neighbour id becomes a block address in the kernels: the encoder
-  // checks them all (the last counter, cleared above, is its flag; searches
-  // clear the counters again before they use them)
-  int bad = 0;
-  int* const flag = idx->counters + kCounters - 1;
-  if (e == hipSuccess) e = qgk::launch_rotate(vectors, n, d, idx->rot, tmp, nullptr, 0, nullptr);
-  if (e == hipSuccess)
-    e = qgk::launch_encode(vectors, tmp, n, d, graph, r, idx->blocks, idx->block_bytes, flag, nullptr);
-  if (e == hipSuccess) e = hipMemcpy(&bad, flag, sizeof bad, hipMemcpyDeviceToHost);  // waits for the encoder
-  (void)hipFree(tmp);
-  if (e != hipSuccess) {
-    release(idx);
-    return hip_fail(e, "encode");
-  }
-  if (bad) {
-    release(idx);
-    return fail(QG_EINVAL, bad & 1 ? "graph id out of range" : "a neighbour list repeats an id");
   }
   *out = idx;
   return QG_OK;

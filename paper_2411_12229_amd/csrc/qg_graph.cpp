@@ -7,13 +7,14 @@
 // pruning rule; every list is replaced at once.  In the last iteration the
 // refinement supplements edges up to R and random ids fill vertices with too
 // few candidates.  Then unreachable vertices are linked from their nearest
-// reachable vertex.
+// reachable vertex; the graph is on the device throughout.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <chrono>
 #include <cstdio>
 #include <cstring>
+#include <new>
 #include <string>
 #include <utility>
 #include <vector>
@@ -44,24 +45,41 @@ int hip_err(hipError_t e, const char* what) {
     if (e_ != hipSuccess) return hip_err(e_, what); \
   } while (0)
 
-// Breadth-first reachability from the entry over rows of r ids (-1 = empty).
-int64_t reach_from(const std::vector<int32_t>& G, int64_t n, int r, int32_t entry, std::vector<char>& seen,
-                   std::vector<int32_t>& queue) {
-  std::fill(seen.begin(), seen.end(), 0);
-  int64_t h = 0, t = 0;
-  queue[t++] = entry;
-  seen[entry] = 1;
-  while (h < t) {
-    const int32_t u = queue[h++];
-    for (int j = 0; j < r; ++j) {
-      const int32_t v = G[(size_t)u * r + j];
-      if (v >= 0 && !seen[v]) {
-        seen[v] = 1;
-        queue[t++] = v;
-      }
-    }
+// Frees an index and the rotated vectors it is encoded from.
+struct Builder {
+  qg_index* idx = nullptr;
+  float* rotated = nullptr;
+  ~Builder() {
+    if (idx) qg_free_index(idx);
+    (void)hipFree(rotated);
   }
-  return t;
+};
+
+constexpr int kLevels = 16;  // breadth-first levels launched between two looks of the host
+
+// Breadth-first reachability from the entry over rows of r ids (-1 = empty):
+// `reached` receives the count, seen one bit per vertex.
+int reach_from(const int32_t* G, int64_t n, int r, int32_t entry, uint32_t* seen, int32_t* queue, int32_t* count,
+               int64_t* reached) {
+  const size_t words = (size_t)(n + 31) / 32;
+  const uint32_t bit = 1u << (entry & 31);
+  int32_t host[kLevels + 1] = {1};
+  HIP_OR_FAIL(hipMemset(seen, 0, sizeof(uint32_t) * words), "reachability");
+  HIP_OR_FAIL(hipMemcpy(seen + (entry >> 5), &bit, sizeof bit, hipMemcpyHostToDevice), "reachability");
+  HIP_OR_FAIL(hipMemcpy(queue, &entry, sizeof entry, hipMemcpyHostToDevice), "reachability");
+  for (int64_t base = 0;;) {
+    for (int l = 1; l <= kLevels; ++l) host[l] = 0;
+    HIP_OR_FAIL(hipMemcpy(count, host, sizeof host, hipMemcpyHostToDevice), "reachability");
+    for (int l = 0; l < kLevels; ++l)
+      HIP_OR_FAIL(qgg::launch_bfs_level(G, r, n, l, base, queue, seen, count, nullptr), "reachability");
+    HIP_OR_FAIL(hipMemcpy(host, count, sizeof host, hipMemcpyDeviceToHost), "reachability");
+    for (int l = 0; l < kLevels; ++l) base += host[l];
+    if (!host[kLevels]) {
+      *reached = base;
+      return QG_OK;
+    }
+    host[0] = host[kLevels];
+  }
 }
 
 class DeviceScope {
@@ -109,10 +127,17 @@ extern "C" int qg_build_graph(const float* vectors, int64_t n, int32_t d, int32_
   HIP_OR_FAIL(sdist.alloc(sizeof(float) * (size_t)(chunk * ef_build)), "hipMalloc search distances");
   HIP_OR_FAIL(hipMemcpy(G.p, init_graph, sizeof(int32_t) * (size_t)(n * r), hipMemcpyDeviceToDevice), "copy graph");
 
+  // one index for the whole build: each graph is encoded into its blocks from
+  // the vectors rotated once
+  Builder B;
+  auto encode = [&]() {
+    int rc = B.idx ? QG_OK : qgi::begin_index(vectors, n, d, r, rotation, entry, device, &B.idx, &B.rotated);
+    return rc ? rc : qgi::encode_index(B.idx, vectors, B.rotated, G.as<int32_t>());
+  };
   for (int it = 0; it < iters; ++it) {
-    qg_index* idx = nullptr;
-    int rc = qg_build_index(vectors, n, d, G.as<int32_t>(), r, rotation, entry, device, &idx);
+    int rc = encode();
     if (rc) return rc;  // the message is set
+    qg_index* const idx = B.idx;
     for (int64_t q0 = 0; q0 < n && rc == QG_OK; q0 += chunk) {
       const int64_t nq = std::min(chunk, n - q0);
       rc = qg_search_ex(idx, vectors + q0 * d, nq, ef_build, ef_build, 0, sids.as<int32_t>(), sdist.as<float>(),
@@ -124,7 +149,6 @@ extern "C" int qg_build_graph(const float* vectors, int64_t n, int32_t d, int32_
       }
     }
     const hipError_t es = hipDeviceSynchronize();
-    qg_free_index(idx);
     if (rc) return rc;
     HIP_OR_FAIL(es, "search and pruning");
     std::swap(G.p, Gnew.p);  // all lists are replaced at once
@@ -143,111 +167,95 @@ extern "C" int qg_build_graph(const float* vectors, int64_t n, int32_t d, int32_
     // order, then w's edges not taken by a repair, farthest first (fp64, ties
     // to the larger id).  Rounds repeat until every vertex is reachable or a
     // round links none.
-    std::vector<int32_t> H((size_t)(n * r));
-    HIP_OR_FAIL(hipMemcpy(H.data(), G.p, sizeof(int32_t) * H.size(), hipMemcpyDeviceToHost), "download graph");
-    std::vector<char> seen((size_t)n), fixed((size_t)(n * r), 0);
-    std::vector<int32_t> queue((size_t)n), unr, ws, ids;
-    std::vector<int64_t> pick;
-    std::vector<double> rowd;
-    DevBuf unr_d, qv_d, ws_d, rowd_d;
-    int64_t cap = 0, wcap = 0;
-    stats[0] = reach_from(H, n, r, entry, seen, queue);
+    // The graph stays on the device; the host only orders the picks.
+    const size_t words = (size_t)(n + 31) / 32;
+    DevBuf seen, queue, count, taken, unr_d, pick_d, qv_d, w_d, off_d, v_d;
+    HIP_OR_FAIL(seen.alloc(sizeof(uint32_t) * words), "hipMalloc reachability");
+    HIP_OR_FAIL(queue.alloc(sizeof(int32_t) * (size_t)n), "hipMalloc reachability");
+    HIP_OR_FAIL(count.alloc(sizeof(int32_t) * (kLevels + 1)), "hipMalloc reachability");
+    HIP_OR_FAIL(taken.alloc(sizeof(uint64_t) * (size_t)n), "hipMalloc repaired slots");
+    HIP_OR_FAIL(hipMemset(taken.p, 0, sizeof(uint64_t) * (size_t)n), "clear repaired slots");
+    std::vector<int32_t> unr, pick, ws, off, vs;
+    std::vector<int64_t> order;
+    int64_t cap = 0;
+    int rc = reach_from(G.as<int32_t>(), n, r, entry, seen.as<uint32_t>(), queue.as<int32_t>(), count.as<int32_t>(),
+                        &stats[0]);
+    if (rc) return rc;
     note("repair, reachable before", 0, stats[0]);
-    for (int round = 0; round < 64; ++round) {
-      const int64_t reached = reach_from(H, n, r, entry, seen, queue);
+    int64_t reached = stats[0];
+    for (int round = 0; round < 64 && reached < n; ++round) {
       if (round) note("repair round, reachable", round, reached);
-      if (reached == n) break;
-      unr.clear();
-      for (int64_t v = 0; v < n; ++v)
-        if (!seen[(size_t)v]) unr.push_back((int32_t)v);
-      const int64_t nu = (int64_t)unr.size();
-      if (nu > cap) {
+      const int64_t nu = n - reached;
+      if (nu > cap) {  // (the first round has the most, but for links that cost a vertex its only way in)
         cap = nu;
-        (void)hipFree(unr_d.p);
-        (void)hipFree(qv_d.p);
-        unr_d.p = qv_d.p = nullptr;
+        for (DevBuf* b : {&unr_d, &pick_d, &qv_d, &w_d, &off_d, &v_d}) {
+          (void)hipFree(b->p);
+          b->p = nullptr;
+        }
         HIP_OR_FAIL(unr_d.alloc(sizeof(int32_t) * (size_t)cap), "hipMalloc");
+        HIP_OR_FAIL(pick_d.alloc(sizeof(int32_t) * (size_t)cap), "hipMalloc");
         HIP_OR_FAIL(qv_d.alloc(sizeof(float) * (size_t)(cap * d)), "hipMalloc");
+        HIP_OR_FAIL(w_d.alloc(sizeof(int32_t) * (size_t)cap), "hipMalloc");
+        HIP_OR_FAIL(off_d.alloc(sizeof(int32_t) * (size_t)(cap + 1)), "hipMalloc");
+        HIP_OR_FAIL(v_d.alloc(sizeof(int32_t) * (size_t)cap), "hipMalloc");
       }
-      HIP_OR_FAIL(hipMemcpy(unr_d.p, unr.data(), sizeof(int32_t) * (size_t)nu, hipMemcpyHostToDevice), "upload");
-      HIP_OR_FAIL(hipMemcpy(G.p, H.data(), sizeof(int32_t) * H.size(), hipMemcpyHostToDevice), "upload graph");
+      HIP_OR_FAIL(hipMemset(count.p, 0, sizeof(int32_t)), "unreachable vertices");
+      HIP_OR_FAIL(qgg::launch_unseen(seen.as<uint32_t>(), n, unr_d.as<int32_t>(), count.as<int32_t>(), nullptr),
+                  "unreachable vertices");
       HIP_OR_FAIL(qgg::launch_gather(vectors, d, unr_d.as<int32_t>(), nu, qv_d.as<float>(), nullptr), "gather");
-      qg_index* idx = nullptr;
-      int rc = qg_build_index(vectors, n, d, G.as<int32_t>(), r, rotation, entry, device, &idx);
-      if (rc) return rc;
-      ids.resize((size_t)(std::min(chunk, nu) * ef_build));
-      pick.assign((size_t)nu, -1);
-      for (int64_t q0 = 0; q0 < nu && rc == QG_OK; q0 += chunk) {
+      if ((rc = encode())) return rc;
+      for (int64_t q0 = 0; q0 < nu; q0 += chunk) {
         const int64_t nq = std::min(chunk, nu - q0);
-        rc = qg_search_ex(idx, qv_d.as<float>() + q0 * d, nq, ef_build, ef_build, 0, sids.as<int32_t>(),
+        rc = qg_search_ex(B.idx, qv_d.as<float>() + q0 * d, nq, ef_build, ef_build, 0, sids.as<int32_t>(),
                           sdist.as<float>(), nullptr);
-        if (rc) break;
-        const hipError_t e = hipMemcpy(ids.data(), sids.p, sizeof(int32_t) * (size_t)(nq * ef_build),
-                                       hipMemcpyDeviceToHost);
-        if (e != hipSuccess) rc = hip_err(e, "download search results");
-        for (int64_t a = 0; a < nq && rc == QG_OK; ++a) {
-          int64_t w = -1;
-          for (int b = 0; b < ef_build && w < 0; ++b) {
-            const int32_t x = ids[(size_t)(a * ef_build + b)];
-            if (x < 0) break;
-            bool free_slot = false;
-            for (int j = 0; j < r && !free_slot; ++j) free_slot = !fixed[(size_t)((int64_t)x * r + j)];
-            if (free_slot) w = x;
+        if (rc) return rc;
+        HIP_OR_FAIL(qgg::launch_pick(sids.as<int32_t>(), nq, ef_build, r, taken.as<unsigned long long>(),
+                                     pick_d.as<int32_t>() + q0, nullptr),
+                    "repair picks");
+      }
+      try {
+        unr.resize((size_t)nu);
+        pick.resize((size_t)nu);
+        order.clear();
+        order.reserve((size_t)nu);
+        ws.clear();
+        off.clear();
+        vs.clear();
+        HIP_OR_FAIL(hipMemcpy(unr.data(), unr_d.p, sizeof(int32_t) * (size_t)nu, hipMemcpyDeviceToHost), "download");
+        HIP_OR_FAIL(hipMemcpy(pick.data(), pick_d.p, sizeof(int32_t) * (size_t)nu, hipMemcpyDeviceToHost), "download");
+        for (int64_t a = 0; a < nu; ++a)
+          if (pick[(size_t)a] >= 0)
+            order.push_back((int64_t)((uint64_t)(uint32_t)pick[(size_t)a] << 32 | (uint32_t)unr[(size_t)a]));
+        std::sort(order.begin(), order.end());
+        for (int64_t x : order) {
+          const int32_t w = (int32_t)(x >> 32);
+          if (ws.empty() || ws.back() != w) {
+            ws.push_back(w);
+            off.push_back((int32_t)vs.size());
           }
-          if (w >= 0) pick[(size_t)(q0 + a)] = (int64_t)((uint64_t)w << 32 | (uint32_t)unr[(size_t)(q0 + a)]);
+          vs.push_back((int32_t)(x & 0xffffffff));
         }
+        off.push_back((int32_t)vs.size());
+      } catch (const std::bad_alloc&) {
+        return qgi::set_error(QG_ENOMEM, "host buffer");
       }
-      qg_free_index(idx);
+      int32_t made = 0;
+      HIP_OR_FAIL(hipMemcpy(w_d.p, ws.data(), sizeof(int32_t) * ws.size(), hipMemcpyHostToDevice), "upload");
+      HIP_OR_FAIL(hipMemcpy(off_d.p, off.data(), sizeof(int32_t) * off.size(), hipMemcpyHostToDevice), "upload");
+      HIP_OR_FAIL(hipMemcpy(v_d.p, vs.data(), sizeof(int32_t) * vs.size(), hipMemcpyHostToDevice), "upload");
+      HIP_OR_FAIL(hipMemset(count.p, 0, sizeof(int32_t)), "links");
+      HIP_OR_FAIL(qgg::launch_link(vectors, d, r, (int64_t)ws.size(), w_d.as<int32_t>(), off_d.as<int32_t>(),
+                                   v_d.as<int32_t>(), G.as<int32_t>(), taken.as<unsigned long long>(),
+                                   count.as<int32_t>(), nullptr),
+                  "links");
+      HIP_OR_FAIL(hipMemcpy(&made, count.p, sizeof made, hipMemcpyDeviceToHost), "links");
+      stats[1] += made;
+      rc = reach_from(G.as<int32_t>(), n, r, entry, seen.as<uint32_t>(), queue.as<int32_t>(), count.as<int32_t>(),
+                      &reached);
       if (rc) return rc;
-      std::sort(pick.begin(), pick.end());
-      ws.clear();
-      for (int64_t x : pick)
-        if (x >= 0 && (ws.empty() || ws.back() != (int32_t)(x >> 32))) ws.push_back((int32_t)(x >> 32));
-      const int64_t nw = (int64_t)ws.size();
-      if (nw > wcap) {
-        wcap = nw;
-        (void)hipFree(ws_d.p);
-        (void)hipFree(rowd_d.p);
-        ws_d.p = rowd_d.p = nullptr;
-        HIP_OR_FAIL(ws_d.alloc(sizeof(int32_t) * (size_t)wcap), "hipMalloc");
-        HIP_OR_FAIL(rowd_d.alloc(sizeof(double) * (size_t)(wcap * r)), "hipMalloc");
-      }
-      rowd.resize((size_t)(nw * r));
-      HIP_OR_FAIL(hipMemcpy(ws_d.p, ws.data(), sizeof(int32_t) * (size_t)nw, hipMemcpyHostToDevice), "upload");
-      HIP_OR_FAIL(qgg::launch_rows_dist(vectors, d, r, ws_d.as<int32_t>(), nw, G.as<int32_t>(), rowd_d.as<double>(),
-                                        nullptr),
-                  "row distances");
-      HIP_OR_FAIL(hipMemcpy(rowd.data(), rowd_d.p, sizeof(double) * rowd.size(), hipMemcpyDeviceToHost), "download");
-      int64_t made = 0;
-      size_t a = 0;
-      while (a < pick.size() && pick[a] < 0) ++a;
-      for (int64_t g = 0; g < nw; ++g) {
-        const int64_t w = ws[(size_t)g];
-        int32_t* row = H.data() + (size_t)(w * r);
-        const double* dr = rowd.data() + (size_t)(g * r);
-        std::vector<int> slots;
-        for (int j = 0; j < r; ++j)
-          if (row[j] < 0) slots.push_back(j);  // empty slots first, in slot order
-        const size_t nempty = slots.size();
-        for (int j = 0; j < r; ++j)
-          if (row[j] >= 0 && !fixed[(size_t)(w * r + j)]) slots.push_back(j);
-        std::stable_sort(slots.begin() + (std::ptrdiff_t)nempty, slots.end(), [&](int x, int y) {
-          return dr[x] > dr[y] || (dr[x] == dr[y] && row[x] > row[y]);  // farthest first, ties to the larger id
-        });
-        size_t next = 0;
-        for (; a < pick.size() && (pick[a] >> 32) == w; ++a) {
-          if (next >= slots.size()) continue;  // no slot left: this v waits for the next round
-          const int j = slots[next++];
-          row[j] = (int32_t)(pick[a] & 0xffffffff);
-          fixed[(size_t)(w * r + j)] = 1;
-          ++stats[1];
-          ++made;
-        }
-      }
       if (!made) break;
     }
-    stats[2] = reach_from(H, n, r, entry, seen, queue);
-    HIP_OR_FAIL(hipMemcpy(G.p, H.data(), sizeof(int32_t) * H.size(), hipMemcpyHostToDevice), "upload graph");
+    stats[2] = reached;
     if (stats[2] != n) return qgi::set_error(QG_EUNSUPPORTED, "connectivity repair could not reach every vertex");
   }
   HIP_OR_FAIL(hipMemcpy(out_graph, G.p, sizeof(int32_t) * (size_t)(n * r), hipMemcpyDeviceToDevice), "copy graph");

@@ -602,16 +602,89 @@ __global__ __launch_bounds__(256) void gather_kernel(const float* __restrict__ X
   out[i] = X[(int64_t)ids[r] * D + c];
 }
 
-// Repair helper: for each listed vertex w, the squared distances from x_w to
-// its R neighbours (+inf for an empty slot).
-__global__ __launch_bounds__(256) void rows_dist_kernel(const float* __restrict__ X, int D, int R,
-                                                        const int32_t* __restrict__ ws, int64_t nw,
-                                                        const int32_t* __restrict__ G, double* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= nw * R) return;
-  const int64_t w = ws[i / R];
-  const int32_t v = G[w * R + i % R];
-  out[i] = v >= 0 ? dist2_seq<8>(X + w * D, X + (int64_t)v * D, D) : __builtin_inf();
+// One level of a breadth-first search: the neighbours of the `size` vertices
+// queue[base, base + size) that are not in `seen` yet enter it and the queue
+// behind them.  Level l of a run of levels (l = level): its size is count[l] and
+// its start `base` plus the sizes of the levels before it, all written by the
+// launches before; the vertices it finds are counted in count[l + 1].  So
+// several levels run without the host (on the host the search of a 50,000 x 32
+// graph took 2 ms, mostly cache misses; here a level takes about 5 us).
+__global__ __launch_bounds__(256) void bfs_level_kernel(const int32_t* __restrict__ G, int R, int64_t n, int level,
+                                                        int64_t base, int32_t* __restrict__ queue,
+                                                        uint32_t* __restrict__ seen, int32_t* count) {
+  for (int l = 0; l < level; ++l) base += count[l];
+  const int64_t size = count[level], next = base + size;
+  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < size * R; e += (int64_t)gridDim.x * 256) {
+    const int32_t v = G[(int64_t)queue[base + e / R] * R + e % R];
+    if (v < 0 || v >= n) continue;
+    const uint32_t bit = 1u << (v & 31);
+    if (seen[v >> 5] & bit) continue;  // a stale word only costs the atomic
+    if (!(atomicOr(seen + (v >> 5), bit) & bit)) queue[next + atomicAdd(count + level + 1, 1)] = v;
+  }
+}
+
+// The vertices not in `seen`, in any order, counted in *count.
+__global__ __launch_bounds__(256) void unseen_kernel(const uint32_t* __restrict__ seen, int64_t n,
+                                                     int32_t* __restrict__ out, int32_t* count) {
+  const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (v < n && !((seen[v >> 5] >> (v & 31)) & 1u)) out[atomicAdd(count, 1)] = (int32_t)v;
+}
+
+// Repair: for each of nq searches (ids[nq][EF], padded with -1) the nearest
+// result that has a slot not taken by a repair, or -1.  One wavefront each;
+// taken[v]: bit j = slot j of v.
+__global__ __launch_bounds__(64) void pick_kernel(const int32_t* __restrict__ ids, int EF, int R,
+                                                  const unsigned long long* __restrict__ taken,
+                                                  int32_t* __restrict__ pick) {
+  const int lane = lane_id();
+  const int32_t* row = ids + (int64_t)blockIdx.x * EF;
+  const unsigned long long full = R >= 64 ? ~0ull : (1ull << R) - 1ull;
+  int32_t w = -1;
+  for (int b = 0; b < EF; b += 64) {
+    const int32_t x = b + lane < EF ? row[b + lane] : -1;
+    const uint64_t m = ballot(x >= 0 && taken[x >= 0 ? x : 0] != full);
+    if (m) {
+      w = __builtin_amdgcn_readlane(x, first_lane(m));
+      break;
+    }
+  }
+  if (lane == 0) pick[blockIdx.x] = w;
+}
+
+// Repair: group g links the vertices v[off[g] .. off[g + 1]) (in that order)
+// from w[g]: they take w's empty slots in slot order, then its edges not taken
+// by a repair, farthest first (fp64, ties to the larger id), while slots are
+// left.  One wavefront per group, lane j slot j (R <= 64); *made counts the
+// links.
+__global__ __launch_bounds__(64) void link_kernel(const float* __restrict__ X, int D, int R,
+                                                  const int32_t* __restrict__ w, const int32_t* __restrict__ off,
+                                                  const int32_t* __restrict__ v, int32_t* __restrict__ G,
+                                                  unsigned long long* __restrict__ taken, int32_t* made) {
+  const int lane = lane_id();
+  const int64_t u = w[blockIdx.x];
+  const int o = off[blockIdx.x], cnt = off[blockIdx.x + 1] - o;
+  const unsigned long long tk = taken[u];
+  const int32_t id = lane < R ? G[u * R + lane] : 0;
+  const bool empty = lane < R && id < 0, edge = lane < R && id >= 0 && !((tk >> lane) & 1ull);
+  const uint64_t em = ballot(empty), ed = ballot(edge);
+  const double d = edge ? dist2_seq<8>(X + u * D, X + (int64_t)id * D, D) : 0.0;
+  int rank = empty ? lanes_below(em) : __popcll(em);
+  for (uint64_t m = ed; m; m &= m - 1) {
+    const int i = first_lane(m);
+    const uint64_t b = (uint64_t)__double_as_longlong(d);
+    const double di = __longlong_as_double(
+        (long long)((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(b >> 32), i) << 32 |
+                    (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, i)));
+    const int32_t ii = __builtin_amdgcn_readlane(id, i);
+    if (edge) rank += di > d || (di == d && ii > id);
+  }
+  const bool use = (empty || edge) && rank < cnt;
+  if (use) G[u * R + lane] = v[o + rank];
+  const uint64_t um = ballot(use);
+  if (lane == 0) {
+    taken[u] = tk | um;
+    atomicAdd(made, __popcll(um));
+  }
 }
 
 hipError_t launch_prune(const float* X, int D, const int32_t* sids, int EF, const int32_t* G, int R, int64_t N,
@@ -647,11 +720,30 @@ hipError_t launch_gather(const float* X, int D, const int32_t* ids, int64_t n, f
   return hipGetLastError();
 }
 
-hipError_t launch_rows_dist(const float* X, int D, int R, const int32_t* ws, int64_t nw, const int32_t* G, double* out,
-                            hipStream_t st) {
-  if (nw <= 0) return hipSuccess;
-  hipLaunchKernelGGL(rows_dist_kernel, dim3((unsigned)((nw * R + 255) / 256)), dim3(256), 0, st, X, D, R, ws, nw, G,
-                     out);
+hipError_t launch_bfs_level(const int32_t* G, int R, int64_t n, int level, int64_t base, int32_t* queue,
+                            uint32_t* seen, int32_t* count, hipStream_t st) {
+  const int64_t blocks = (n * R + 255) / 256;
+  hipLaunchKernelGGL(bfs_level_kernel, dim3((unsigned)(blocks < 2048 ? blocks : 2048)), dim3(256), 0, st, G, R, n, level,
+                     base, queue, seen, count);
+  return hipGetLastError();
+}
+
+hipError_t launch_unseen(const uint32_t* seen, int64_t n, int32_t* out, int32_t* count, hipStream_t st) {
+  hipLaunchKernelGGL(unseen_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, seen, n, out, count);
+  return hipGetLastError();
+}
+
+hipError_t launch_pick(const int32_t* ids, int64_t nq, int EF, int R, const unsigned long long* taken, int32_t* pick,
+                       hipStream_t st) {
+  if (nq <= 0) return hipSuccess;
+  hipLaunchKernelGGL(pick_kernel, dim3((unsigned)nq), dim3(64), 0, st, ids, EF, R, taken, pick);
+  return hipGetLastError();
+}
+
+hipError_t launch_link(const float* X, int D, int R, int64_t groups, const int32_t* w, const int32_t* off,
+                       const int32_t* v, int32_t* G, unsigned long long* taken, int32_t* made, hipStream_t st) {
+  if (groups <= 0) return hipSuccess;
+  hipLaunchKernelGGL(link_kernel, dim3((unsigned)groups), dim3(64), 0, st, X, D, R, w, off, v, G, taken, made);
   return hipGetLastError();
 }
 
