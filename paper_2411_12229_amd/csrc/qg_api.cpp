@@ -109,7 +109,7 @@ static int alloc_common(qg_index* idx) {
   HIP_TRY(hipMalloc(&idx->blocks, (size_t)(idx->N * idx->block_bytes)), "hipMalloc blocks");
   HIP_TRY(hipMalloc(&idx->counters, sizeof(int) * kCounters), "hipMalloc counters");
   HIP_TRY(hipMemset(idx->counters, 0, sizeof(int) * kCounters), "hipMemset counters");
-  idx->fb_slots = 64;
+  idx->fb_slots = qgk::kBitsets;
   idx->fb_words = (idx->N + 31) / 32;
   HIP_TRY(hipMalloc(&idx->fb_bits, sizeof(uint32_t) * (size_t)(idx->fb_words * idx->fb_slots)), "hipMalloc bitsets");
   return QG_OK;
@@ -590,8 +590,12 @@ static int search_impl(const qg_index* cidx, const float* queries, int64_t nq, i
   const int lb = (idx->lut32 && (ls == 0 || ls == 3) && !qgl::use_planes(idx->D, idx->R)) ? 4 : 2;
   const int nb = (idx->beam_regs && !(flags & QG_SEARCH_LDS_BEAM)) ? qgk::beam_regs(false, ls, ef, idx->N, idx->D, nq) : 0;
   // NN needs LDS only where it outgrows its registers
-  const int k_cap = k <= 64 * qgk::nn_regs(nb) ? 0 : k_cap_all;
+  int k_cap = k <= 64 * qgk::nn_regs(nb) ? 0 : k_cap_all;
   const int k_cap_ov = k <= 64 * qgk::nn_regs(0) ? 0 : k_cap_all;
+  // few queries: one launch, in which a query that outgrows its table runs again
+  // at once (its area must then serve both searches)
+  const bool inl = nq <= qgk::kBitsets && (ls == 0 || ls == 3) && lb == 2;
+  if (inl) k_cap = std::max(k_cap, k_cap_ov);
   a.k_cap = k_cap;
   const qgl::SearchLds L = qgl::search_lds(idx->D, idx->R, ef_cap, 1 << hbits, k_cap, lb);
   const qgl::SearchLds Lf = qgl::search_lds(idx->D, idx->R, ef_cap, 0, k_cap_ov);
@@ -604,11 +608,14 @@ static int search_impl(const qg_index* cidx, const float* queries, int64_t nq, i
   while (wpb > 1 && (size_t)wpb * L.total + extra > lds_cap) wpb >>= 1;
   if ((size_t)L.total + extra > lds_cap) return fail(QG_EUNSUPPORTED, "per-query LDS exceeds the device limit");
   const size_t lds = (size_t)wpb * L.total + extra;
-  int occ = qgk::search_occupancy(idx->D, idx->R, false, ls, nb, lb, wpb, lds);
-  if (occ <= 0) occ = 1;
-  if (idx->cu_waves > 0) occ = std::min(occ, std::max(1, idx->cu_waves / wpb));
   int64_t want = (nq + wpb - 1) / wpb;
-  int grid = (int)std::min<int64_t>(want, (int64_t)occ * idx->cus);
+  int grid = (int)want;
+  if (!inl) {  // (at most kBitsets / wpb workgroups need no count of what fits)
+    int occ = qgk::search_occupancy(idx->D, idx->R, qgk::kMainPass, ls, nb, lb, wpb, lds);
+    if (occ <= 0) occ = 1;
+    if (idx->cu_waves > 0) occ = std::min(occ, std::max(1, idx->cu_waves / wpb));
+    grid = (int)std::min<int64_t>(want, (int64_t)occ * idx->cus);
+  }
 
   // the rotation's first workgroup also clears the queue counters (a kernel,
   // not a memset, so the call can be captured into a graph)
@@ -617,11 +624,14 @@ static int search_impl(const qg_index* cidx, const float* queries, int64_t nq, i
           "rotate queries");
   if (!fx && (rc = record(idx, 0, false))) return rc;
   if (!fx && (rc = record(idx, 1, true))) return rc;
-  HIP_TRY(qgk::launch_search(idx->D, idx->R, false, ls, nb, lb, a, grid, wpb, lds, idx->stream), "search");
+  HIP_TRY(qgk::launch_search(idx->D, idx->R, inl ? qgk::kInlinePass : qgk::kMainPass, ls, nb, lb, a, grid, wpb, lds,
+                             idx->stream),
+          "search");
   if (!fx && (rc = record(idx, 1, false))) return rc;
+  if (inl) return QG_OK;
   // overflow pass: one wavefront per workgroup, one bitset each
   a.k_cap = k_cap_ov;
-  HIP_TRY(qgk::launch_search(idx->D, idx->R, true, ls, 0, 2, a, idx->fb_slots, 1, (size_t)Lf.total + extra,
+  HIP_TRY(qgk::launch_search(idx->D, idx->R, qgk::kOverflowPass, ls, 0, 2, a, idx->fb_slots, 1, (size_t)Lf.total + extra,
                              idx->stream),
           "search overflow pass");
   return QG_OK;

@@ -77,9 +77,13 @@ int beam_regs(bool overflow_pass, int ls_mode, int ef_bound, int64_t n, int D, i
 // NN registers per lane of a kernel with nb beam registers (nb 0: beam in LDS);
 // larger k keep NN in LDS
 constexpr int nn_regs(int nb) { return nb >= 3 ? nb : 1; }
-hipError_t launch_search(int D, int R, bool overflow_pass, int ls_mode, int nb, int lb, const SearchArgs& a, int grid,
+// kMainPass with kOverflowPass after it, or kInlinePass alone (plain and mixed
+// modes, int16 table; at most kBitsets queries, one a wavefront at most).
+enum SearchPass { kMainPass, kOverflowPass, kInlinePass };
+constexpr int kBitsets = 64;  // N-bit sets an index holds
+hipError_t launch_search(int D, int R, SearchPass pass, int ls_mode, int nb, int lb, const SearchArgs& a, int grid,
                          int wpb, size_t lds, hipStream_t st);
-int search_occupancy(int D, int R, bool overflow_pass, int ls_mode, int nb, int lb, int wpb, size_t lds);
+int search_occupancy(int D, int R, SearchPass pass, int ls_mode, int nb, int lb, int wpb, size_t lds);
 constexpr size_t mlp_lds_bytes() { return 2 * 64 * 16 + 8 * 64 * 16 + 3 * 128 + 16; }
 hipError_t launch_estimate(int D, int R, const EstimateArgs& a, int64_t nq, hipStream_t st);
 

@@ -1104,8 +1104,10 @@ __device__ __forceinline__ T rdlane(const T (&b)[NB], int r, int l) {
   return v;
 }
 
+// Runs query q; true unless its visited set outgrew the on-chip table, when
+// nothing has been written for it (never with GV).
 template <int D, int R, bool GV, int LS, int LB>
-__device__ void search_one(const SearchArgs& a, int64_t q, uint8_t* lds, const qgl::SearchLds& L, uint32_t* gbits,
+__device__ bool search_one(const SearchArgs& a, int64_t q, uint8_t* lds, const qgl::SearchLds& L, uint32_t* gbits,
                            const uint8_t* mlp) {
   using BV = BlockView<D, R>;
   constexpr int DPL = BV::DPL;
@@ -1124,7 +1126,7 @@ __device__ void search_one(const SearchArgs& a, int64_t q, uint8_t* lds, const q
         a.out_dists[q * a.k_out + i] = __builtin_inff();
       }
       if (a.out_stats && lane < 4) a.out_stats[4 * q + lane] = lane == 3 ? -1 : 0;
-      return;
+      return true;
     }
   }
   void* lut = lds + L.lut;
@@ -1272,13 +1274,7 @@ __device__ void search_one(const SearchArgs& a, int64_t q, uint8_t* lds, const q
         if (lane == 0) vis.tab[p_slot] = p;  // p is absent: its probe ended at this empty slot
         wave_sync();
       }
-      if (++nvis > vis_limit) {  // on-chip visited set full: hand the query to the overflow path
-        if (lane == 0) {
-          const int slot = atomicAdd(a.counters + 1, 1);
-          a.overflow_list[slot] = (int32_t)q;
-        }
-        return;
-      }
+      if (++nvis > vis_limit) return false;  // on-chip visited set full
     }
     ++expansions;
 
@@ -1298,13 +1294,7 @@ __device__ void search_one(const SearchArgs& a, int64_t q, uint8_t* lds, const q
     bool valid = (lane % LPN == 0) && b.nb >= 0;
     if constexpr (no_me<LS>) {
       if constexpr (!GV) {
-        if (nvis + (int)__popcll(ballot(valid)) > vis_limit) {  // the set could fill: overflow path
-          if (lane == 0) {
-            const int slot = atomicAdd(a.counters + 1, 1);
-            a.overflow_list[slot] = (int32_t)q;
-          }
-          return;
-        }
+        if (nvis + (int)__popcll(ballot(valid)) > vis_limit) return false;  // the set could fill
       }
       if (valid) valid = seen_insert<GV>(vis, nb);
       nvis += (int)__popcll(ballot(valid));
@@ -1590,6 +1580,7 @@ __device__ void search_one(const SearchArgs& a, int64_t q, uint8_t* lds, const q
     st[2] = appended;
     st[3] = GV ? 1 : 0;
   }
+  return true;
 }
 
 // Algorithm 1 with the beam in registers (ef up to 64 NB): lane i holds beam
@@ -1603,7 +1594,7 @@ __device__ void search_one(const SearchArgs& a, int64_t q, uint8_t* lds, const q
 // bookkeeping (flags, pop count, the next unconsumed entry) then runs on the
 // merged beam.  Results and counters equal those of search_one.
 template <int D, int R, int LS, int NB, int LB>
-__device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, const qgl::SearchLds& L,
+__device__ bool search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, const qgl::SearchLds& L,
                               const uint8_t* mlp) {
   using BV = BlockView<D, R>;
   constexpr int DPL = BV::DPL;
@@ -1622,7 +1613,7 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
         a.out_dists[q * a.k_out + i] = __builtin_inff();
       }
       if (a.out_stats && lane < 4) a.out_stats[4 * q + lane] = lane == 3 ? -1 : 0;
-      return;
+      return true;
     }
   }
   void* lut = lds + L.lut;
@@ -1794,13 +1785,7 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
         visited_add_absent(vis, p, pslot, lane);  // 64 occupied slots in a row (the table is at most half full)
       }
     }
-    if (++nvis > vis_limit) {  // on-chip visited set full: hand the query to the overflow path
-      if (lane == 0) {
-        const int slot = atomicAdd(a.counters + 1, 1);
-        a.overflow_list[slot] = (int32_t)q;
-      }
-      return;
-    }
+    if (++nvis > vis_limit) return false;  // on-chip visited set full
     ++expansions;
 
     // visited filter: the probes that met four other ids go on to the next
@@ -2012,6 +1997,7 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
     st[2] = appended;
     st[3] = 0;
   }
+  return true;
 }
 
 // Minimum wavefronts per SIMD the register allocator must allow (1: no
@@ -2026,8 +2012,9 @@ __device__ void search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
 // registers at D = 128, R = 32 (one query or a mixed batch): 6 as well (107-115
 // registers and 4 wavefronts otherwise; 48-84 bytes of scratch; 6-16% faster).  Measured not to pay: 4 for D = 768 (32
 // bytes of scratch, 1-2% slower); R = 64 would spill over 100 bytes.
-template <int D, int R, int LS, int NB>
+template <int D, int R, int LS, int NB, bool INL>
 constexpr int waves_hint() {
+  if constexpr (INL) return 1;  // few queries: nothing to be resident beside
   if constexpr (NB > 4) return D <= 256 ? 3 : 1;
   if constexpr (NB > 2) return D <= 256 ? 4 : 1;
   if constexpr (NB > 0) {
@@ -2049,9 +2036,14 @@ constexpr int waves_hint() {
 // For the narrow shapes the stop-only and mixed-batch kernels hold their
 // registers to 80, so that 6 wavefronts per SIMD fit (LDS sets residency for
 // the stop-only kernels anyway).
-template <int D, int R, bool GV, int LS, int NB, int LB>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(waves_hint<D, R, LS, NB>()))) void search_kernel(
-    SearchArgs a) {
+// INL: batches of at most as many queries as there are bitsets, each wavefront
+//             with one query at most: a query that outgrows its table is run
+//             again at once by its wavefront, in bitset `wid`, so that no
+//             overflow pass follows (a launch of 4.6 us and its gap, of 54 us
+//             for one query at 128 x 32).
+template <int D, int R, bool GV, int LS, int NB, int LB, bool INL>
+__global__ __launch_bounds__(512)
+    __attribute__((amdgpu_waves_per_eu(waves_hint<D, R, LS, NB, INL>()))) void search_kernel(SearchArgs a) {
   extern __shared__ __align__(16) uint8_t smem[];
   const int wave = uni((int)(threadIdx.x >> 6));
   const int lane = lane_id();
@@ -2063,7 +2055,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(waves_hint<
     __syncthreads();
   }
   const int wid = blockIdx.x * (blockDim.x >> 6) + wave;
-  uint32_t* gbits = GV ? a.fb_bits + (int64_t)wid * a.fb_words : nullptr;
+  uint32_t* gbits = GV || INL ? a.fb_bits + (int64_t)wid * a.fb_words : nullptr;
   int* ctr = a.counters + (GV ? 2 : 0);
   const int64_t limit = GV ? (int64_t)__hip_atomic_load(a.counters + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
                            : a.nq;
@@ -2074,10 +2066,19 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(waves_hint<
   const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x >> 6);
   for (int64_t qi = wid; qi < limit;) {
     const int64_t q = GV ? (int64_t)a.overflow_list[qi] : qi;
+    bool done;
     if constexpr (NB > 0)
-      search_one_rb<D, R, LS, NB, LB>(a, q, lds, L, mlp);
+      done = search_one_rb<D, R, LS, NB, LB>(a, q, lds, L, mlp);
     else
-      search_one<D, R, GV, LS, LB>(a, q, lds, L, gbits, mlp);
+      done = search_one<D, R, GV, LS, LB>(a, q, lds, L, gbits, mlp);
+    if (!done) {
+      if constexpr (INL) {
+        search_one<D, R, true, LS, LB>(a, q, lds, L, gbits, mlp);
+      } else if (lane == 0) {  // the overflow pass takes it
+        const int slot = atomicAdd(a.counters + 1, 1);
+        a.overflow_list[slot] = (int32_t)q;
+      }
+    }
     int c = 0;
     if (lane == 0) c = atomicAdd(ctr, 1);
     qi = nwaves + __builtin_amdgcn_readlane(c, 0);
@@ -2088,9 +2089,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(waves_hint<
 
 // ------------------------------------------- launchers of one dimension
 
-template <int D, int R, bool GV, int LS, int NB, int LB>
+template <int D, int R, bool GV, int LS, int NB, int LB, bool INL>
 static hipError_t launch_search_t(const SearchArgs& a, int grid, int wpb, size_t lds, hipStream_t st) {
-  auto kern = search_kernel<D, R, GV, LS, NB, LB>;
+  auto kern = search_kernel<D, R, GV, LS, NB, LB, INL>;
   if (lds > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -2100,10 +2101,10 @@ static hipError_t launch_search_t(const SearchArgs& a, int grid, int wpb, size_t
   return hipGetLastError();
 }
 
-template <int D, int R, bool GV, int LS, int NB, int LB>
+template <int D, int R, bool GV, int LS, int NB, int LB, bool INL>
 static int occupancy_t(int wpb, size_t lds) {
   int nb = 0;
-  auto kern = search_kernel<D, R, GV, LS, NB, LB>;
+  auto kern = search_kernel<D, R, GV, LS, NB, LB, INL>;
   if (lds > 64 * 1024)
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)lds);
@@ -2116,18 +2117,18 @@ struct LaunchOp {
   int grid, wpb;
   size_t lds;
   hipStream_t st;
-  template <int D, int R, bool GV, int LS, int NB, int LB>
+  template <int D, int R, bool GV, int LS, int NB, int LB, bool INL = false>
   hipError_t run() const {
-    return launch_search_t<D, R, GV, LS, NB, LB>(*a, grid, wpb, lds, st);
+    return launch_search_t<D, R, GV, LS, NB, LB, INL>(*a, grid, wpb, lds, st);
   }
 };
 
 struct OccupancyOp {
   int wpb;
   size_t lds;
-  template <int D, int R, bool GV, int LS, int NB, int LB>
+  template <int D, int R, bool GV, int LS, int NB, int LB, bool INL = false>
   int run() const {
-    return occupancy_t<D, R, GV, LS, NB, LB>(wpb, lds);
+    return occupancy_t<D, R, GV, LS, NB, LB, INL>(wpb, lds);
   }
 };
 
@@ -2137,7 +2138,22 @@ struct OccupancyOp {
 // kernels keep the beam in LDS.  The int32 LUT (lb 4) exists for the main
 // pass of the plain and mixed modes (the ones the autotuner times).
 template <int D, int R, class Op, class Ret>
-static Ret dispatch_mode(bool gv, int ls, int nb, int lb, const Op& op, Ret bad) {
+static Ret dispatch_mode(SearchPass pass, int ls, int nb, int lb, const Op& op, Ret bad) {
+  const bool gv = pass == kOverflowPass;
+  if (pass == kInlinePass) {
+#define QG_NB(ls_)                                                                                                   \
+  (nb == 1   ? op.template run<D, R, false, ls_, 1, 2, true>()                                                      \
+   : nb == 2 ? op.template run<D, R, false, ls_, 2, 2, true>()                                                      \
+   : nb == 3 ? op.template run<D, R, false, ls_, 3, 2, true>()                                                      \
+   : nb == 4 ? op.template run<D, R, false, ls_, 4, 2, true>()                                                      \
+   : nb == 6 ? op.template run<D, R, false, ls_, 6, 2, true>()                                                      \
+   : nb == 8 ? op.template run<D, R, false, ls_, 8, 2, true>() : op.template run<D, R, false, ls_, 0, 2, true>())
+    if (lb != 2) return bad;
+    if (ls == kLsOff) return QG_NB(kLsOff);
+    if (ls == kMixed) return QG_NB(kMixed);
+    return bad;
+#undef QG_NB
+  }
   if (gv) {
     if (lb != 2) return bad;
     switch (ls) {
@@ -2181,18 +2197,18 @@ static Ret dispatch_mode(bool gv, int ls, int nb, int lb, const Op& op, Ret bad)
 #define QG_JOIN2(a, b) a##b
 #define QG_JOIN(a, b) QG_JOIN2(a, b)
 
-hipError_t QG_JOIN(launch_search_, QG_DIM)(int R, bool overflow_pass, int ls_mode, int nb, int lb, const SearchArgs& a,
+hipError_t QG_JOIN(launch_search_, QG_DIM)(int R, SearchPass pass, int ls_mode, int nb, int lb, const SearchArgs& a,
                                            int grid, int wpb, size_t lds, hipStream_t st) {
   const LaunchOp op{&a, grid, wpb, lds, st};
-  if (R == 32) return dispatch_mode<QG_DIM, 32>(overflow_pass, ls_mode, nb, lb, op, hipErrorInvalidValue);
-  if (R == 64) return dispatch_mode<QG_DIM, 64>(overflow_pass, ls_mode, nb, lb, op, hipErrorInvalidValue);
+  if (R == 32) return dispatch_mode<QG_DIM, 32>(pass, ls_mode, nb, lb, op, hipErrorInvalidValue);
+  if (R == 64) return dispatch_mode<QG_DIM, 64>(pass, ls_mode, nb, lb, op, hipErrorInvalidValue);
   return hipErrorInvalidValue;
 }
 
-int QG_JOIN(search_occupancy_, QG_DIM)(int R, bool overflow_pass, int ls_mode, int nb, int lb, int wpb, size_t lds) {
+int QG_JOIN(search_occupancy_, QG_DIM)(int R, SearchPass pass, int ls_mode, int nb, int lb, int wpb, size_t lds) {
   const OccupancyOp op{wpb, lds};
-  if (R == 32) return dispatch_mode<QG_DIM, 32>(overflow_pass, ls_mode, nb, lb, op, 0);
-  if (R == 64) return dispatch_mode<QG_DIM, 64>(overflow_pass, ls_mode, nb, lb, op, 0);
+  if (R == 32) return dispatch_mode<QG_DIM, 32>(pass, ls_mode, nb, lb, op, 0);
+  if (R == 64) return dispatch_mode<QG_DIM, 64>(pass, ls_mode, nb, lb, op, 0);
   return 0;
 }
 
@@ -2312,24 +2328,24 @@ int beam_regs(bool overflow_pass, int ls_mode, int ef_bound, int64_t n, int D, i
 
 #define QG_DIMS(X) X(96) X(128) X(768) X(960)
 #define QG_DECL(d)                                                                                            \
-  hipError_t launch_search_##d(int R, bool overflow_pass, int ls_mode, int nb, int lb, const SearchArgs& a,   \
+  hipError_t launch_search_##d(int R, SearchPass pass, int ls_mode, int nb, int lb, const SearchArgs& a,   \
                                int grid, int wpb, size_t lds, hipStream_t st);                                \
-  int search_occupancy_##d(int R, bool overflow_pass, int ls_mode, int nb, int lb, int wpb, size_t lds);
+  int search_occupancy_##d(int R, SearchPass pass, int ls_mode, int nb, int lb, int wpb, size_t lds);
 QG_DIMS(QG_DECL)
 #undef QG_DECL
 
-hipError_t launch_search(int D, int R, bool overflow_pass, int ls_mode, int nb, int lb, const SearchArgs& a,
+hipError_t launch_search(int D, int R, SearchPass pass, int ls_mode, int nb, int lb, const SearchArgs& a,
                          int grid, int wpb, size_t lds, hipStream_t st) {
 #define QG_CASE(d) \
-  if (D == d) return launch_search_##d(R, overflow_pass, ls_mode, nb, lb, a, grid, wpb, lds, st);
+  if (D == d) return launch_search_##d(R, pass, ls_mode, nb, lb, a, grid, wpb, lds, st);
   QG_DIMS(QG_CASE)
 #undef QG_CASE
   return hipErrorInvalidValue;
 }
 
-int search_occupancy(int D, int R, bool overflow_pass, int ls_mode, int nb, int lb, int wpb, size_t lds) {
+int search_occupancy(int D, int R, SearchPass pass, int ls_mode, int nb, int lb, int wpb, size_t lds) {
 #define QG_CASE(d) \
-  if (D == d) return search_occupancy_##d(R, overflow_pass, ls_mode, nb, lb, wpb, lds);
+  if (D == d) return search_occupancy_##d(R, pass, ls_mode, nb, lb, wpb, lds);
   QG_DIMS(QG_CASE)
 #undef QG_CASE
   return 0;

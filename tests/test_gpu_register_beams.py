@@ -69,3 +69,22 @@ def test_mixed_rows_equal_oracle(made, D, R, k_max, ef_max):
         oi, od = oracle.search(blocks, D, R, e, M, Q[i:i + 1], k, int(efs[i]))
         assert np.array_equal(ids[i, :k], oi[0]) and np.array_equal(dists[i, :k], od[0])
         assert (ids[i, k:] == -1).all() and np.isinf(dists[i, k:]).all()
+
+
+@pytest.mark.parametrize("D,R", [(96, 32), (128, 64), (960, 64)])
+@pytest.mark.parametrize("nq", [1, 7, 40, 64, 65, 130])
+@pytest.mark.parametrize("k,ef", [(10, 48), (100, 200), (70, 600)])
+def test_overflowing_queries(made, D, R, nq, k, ef):
+    """Queries that outgrow the on-chip visited set, in one launch (at most 64 queries) and in the overflow pass."""
+    idx, blocks, M, e, Q = made(D, R)
+    q = np.concatenate([Q] * 4)[:nq]
+    ids, dists, st = idx.search(T(q), k, ef, flags=qg.QG_SEARCH_SMALL_HASH, stats=True)
+    oi, od, os_ = oracle.search(blocks, D, R, e, M, Q, k, ef, with_stats=True)
+    oi, od, os_ = (np.concatenate([x] * 4)[:nq] for x in (oi, od, os_))
+    print(f"D={D} R={R} nq={nq} k={k} ef={ef}: {int((st[:, 3] == 1).sum())} overflowed", flush=True)
+    assert (ef == 48 or (st[:, 3] == 1).any())
+    assert np.array_equal(ids.cpu().numpy(), oi) and np.array_equal(dists.cpu().numpy(), od)
+    assert np.array_equal(st.cpu().numpy()[:, :3], os_[:, :3])
+    ks, efs = np.full(nq, k, np.int32), np.full(nq, ef, np.int32)
+    ids, dists = idx.search_mixed(T(q), T(ks), T(efs), k_max=k, ef_max=ef, flags=qg.QG_SEARCH_SMALL_HASH)
+    assert np.array_equal(ids.cpu().numpy(), oi) and np.array_equal(dists.cpu().numpy(), od)
