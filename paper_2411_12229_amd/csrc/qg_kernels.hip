@@ -2302,25 +2302,25 @@ hipError_t launch_encode(const float* X, const float* ROT, int64_t N, int D, con
   return hipErrorInvalidValue;
 }
 
-// Beam registers per lane for a bound on ef.  Measured, register beam against
-// LDS beam in one call: one register (ef 48, 1M x 128, 10,000 queries) 11-14%
-// faster in the plain, mixed and stop-only kernels; two tie or win in the plain
-// and mixed kernels and lose 6% in the stop-only kernel (whose MLP already
-// holds many registers); three (ef 192, 300,000 x 96) 293 against 386 us for
-// one query, 538 against 660 us for 3,001 queries, 1,251 against 1,376 us for
-// 10,000; four (ef 250) 413 against 518, 778 against 893 and 1,767 against
-// 1,845 us.  The LDS merge's binary searches are a chain of dependent reads,
-// the register merge one pass over the candidates.  Six and eight registers
-// (ef up to 384 and 512) always for the wide shapes (960 x 64: 1,000 queries at
-// ef 384 1,504 against 1,026 us, 10,000 7,073 against 5,258), and for the
-// narrow ones while the batch is resident at once, at three wavefronts a SIMD:
-// there 96 x 32 takes 1,241 against 828 us at ef 384 and 1,000 queries, but
-// 128 x 32 at ef 512 and 10,000 queries 3,314 against 3,652, for the LDS beam
-// fits five wavefronts.
+// Beam registers per lane for a bound on ef, in the plain, mixed and stop modes.
+// Measured, LDS beam against register beam, k 10: the LDS merge's binary
+// searches are a chain of dependent reads, the register merge one pass over the
+// candidates.  One register (ef 48, 128 x 32): 128 against 108 us for 1,000
+// queries.  Two (ef 96, 60,000 queries) 2,170 against 1,940 us at their best.
+// Three (ef 192, 300,000 x 96) 381 against 263 us for one query, 1,374 against
+// 1,098 us for 10,000; four (ef 250) 517 against 378 and 1,842 against 1,586 us.
+// With the stop, which holds more registers: 358 against 262 us (ef 48, 128 x
+// 32, 10,000 queries), 460 against 386 (ef 96), 705 against 562 (ef 192); 1,885
+// against 1,619 us at 960 x 64, ef 192.  Six and eight registers (ef up to 384
+// and 512) always for the wide shapes (960 x 64: 1,000 queries at ef 384 1,504
+// against 1,026 us, 10,000 7,073 against 5,258), and for the narrow ones while
+// the batch is resident at once, at three wavefronts a SIMD: there 96 x 32
+// takes 1,241 against 828 us at ef 384 and 1,000 queries, but 128 x 32 at ef 512
+// and 10,000 queries 3,314 against 3,652, for the LDS beam fits five
+// wavefronts.
 int beam_regs(bool overflow_pass, int ls_mode, int ef_bound, int64_t n, int D, int64_t nq) {
   if (overflow_pass || ls_mode == kLsTrace || ls_mode == kNoMe || n > (int64_t)kIdMask30) return 0;
   if (ef_bound <= 64) return 1;
-  if (ls_mode != kLsOff && ls_mode != kMixed) return 0;
   if (ef_bound <= 256) return (ef_bound + 63) / 64;
   if (ef_bound > 512 || (D <= 256 && nq > 3 * 1024)) return 0;
   return ef_bound <= 384 ? 6 : 8;

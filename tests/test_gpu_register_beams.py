@@ -88,3 +88,22 @@ def test_overflowing_queries(made, D, R, nq, k, ef):
     ks, efs = np.full(nq, k, np.int32), np.full(nq, ef, np.int32)
     ids, dists = idx.search_mixed(T(q), T(ks), T(efs), k_max=k, ef_max=ef, flags=qg.QG_SEARCH_SMALL_HASH)
     assert np.array_equal(ids.cpu().numpy(), oi) and np.array_equal(dists.cpu().numpy(), od)
+
+
+@pytest.mark.parametrize("D,R", [(96, 32), (128, 64), (768, 32)])
+@pytest.mark.parametrize("k,ef", [(10, 65), (10, 128), (70, 130), (100, 193), (10, 256), (200, 300), (10, 512)])
+def test_stop_equals_oracle(made, D, R, k, ef):
+    """The learned stop with every beam storage: a model that stops some queries early."""
+    idx, blocks, M, e, Q = made(D, R)
+    g = np.random.Generator(np.random.PCG64(5))
+    w = [0.05 * g.standard_normal(n) for n in (64 * 16, 64, 64 * 64, 64, 64)] + [np.array([-1.0])]
+    w[0][3], w[2][0], w[4][0] = 1.0, 1.0, 1.5  # mostly: expansions since the results changed
+    bits = torch.from_numpy(np.concatenate(w)).to(torch.bfloat16).view(torch.int16)
+    print(f"stop D={D} R={R} k={k} ef={ef}", flush=True)
+    oi, od, os_, _ = oracle.search_ls(blocks, D, R, e, M, Q, k, ef, w=bits.numpy().view(np.uint16), theta=0.0, t_min=4,
+                                      t_every=3)
+    for flags in (0, qg.QG_SEARCH_LDS_BEAM):
+        ids, dists, st, _ = idx.search_stop(T(Q), k, ef, bits.to(DEV), theta=0.0, t_min=4, t_every=3, flags=flags,
+                                            stats=True)
+        assert np.array_equal(ids.cpu().numpy(), oi) and np.array_equal(dists.cpu().numpy(), od)
+        assert np.array_equal(st.cpu().numpy()[:, :3], os_[:, :3])
