@@ -65,10 +65,11 @@ constexpr float kUnitScale = 4096.0f;                        // f16 elements hol
 // dimensions, and before that the sort; occ: row w's bits over the 32-blocks
 // from its own on; per candidate: exact distance, t value, id, the two scaled
 // norms and the largest approximate cosine.
+// stash: every thread's open pairs of `passes` passes (T tiles each).
 struct PruneLds {
-  int stage, occ, cd, tv, id, rw, hv, cmax, queue, kept, total;
+  int stage, occ, cd, tv, id, rw, hv, cmax, queue, kept, stash, total;
 };
-__host__ __device__ inline PruneLds prune_lds(int C, int R, int KC) {
+__host__ __device__ inline PruneLds prune_lds(int C, int R, int KC, int T, int passes) {
   const int nt = (C + 31) / 32, Cp = 32 * nt;
   int P = 1;
   while (P < C) P <<= 1;
@@ -85,6 +86,8 @@ __host__ __device__ inline PruneLds prune_lds(int C, int R, int KC) {
   s.cmax = o;   o += 4 * Cp;
   s.queue = o;  o += 4 * 128 * kPruneWaves;
   s.kept = o;   o += 4 * R + 4 * 64 + 16;  // kept ids, kept bits, scalars
+  s.stash = (o + 15) & ~15;
+  o = s.stash + 4 * kPruneThreads * ((T + 1) / 2) * passes;
   s.total = (o + 15) & ~15;
   return s;
 }
@@ -147,20 +150,22 @@ __device__ __forceinline__ double dot_seq(const float* __restrict__ xw, const fl
 // that line is decided, and only a cosine within twice the error of its
 // column's largest can be that column's largest.  The pairs that are left
 // (about one in a hundred) are computed as the rules state them, in fp64, by
-// lanes in parallel; every decision and every t_v is therefore exactly that of
+// lanes in parallel, for the refinement only in the columns whose largest
+// cosine is near the threshold; every decision is therefore exactly that of
 // the fp64 rule.  What remains of the NSG scan is one AND of a bit row per
 // kept vertex.
 //
 // Computing every tested pair in fp64 by one lane each is what bound the
 // pruning before: 50,000 x 128 at 232 candidates took 123 ms for the
 // refinement, 4.4 ms per NSG pass and 2.9 ms for the candidate lists, and
-// takes 5.3 ms per iteration now, refinement included; 6,001 x 960 at 214
-// candidates 287, 8.6 and 1.5 ms, now 4.45 ms.  What bounds it now: at 960
-// dimensions the rows' bytes (about 5 MB a vertex with the exact sums, 6 TB/s
-// through L2 and the last-level cache); at 128 latency, two workgroups a
-// compute unit, of 129,000 cycles each 30,000 for the products with their
-// loads, 28,000 for the exact sums, 18,000 for the comparisons, 15,000 for the
-// distances, 12,000 for the order.
+// takes 5.0 ms per iteration now, refinement included; 6,001 x 960 at 214
+// candidates 287, 8.6 and 1.5 ms, now 3.3 ms (4.45 while every column's largest
+// cosine was computed exactly).  What bounds it now: at 960 dimensions the
+// rows' bytes (about 3 MB a vertex, 6 TB/s through L2 and the last-level
+// cache); at 128 latency, two workgroups a compute unit, of about 120,000
+// cycles each 30,000 for the products with their loads, 18,000 for the
+// comparisons, 15,000 for the distances, 15,000 for the exact sums, 12,000 for
+// the order.
 // T: 32 x 32 tiles of cosines a wavefront holds in one pass over the
 // dimensions (16 registers each).
 struct PruneArgs {
@@ -172,6 +177,7 @@ struct PruneArgs {
   int32_t* Gout;  // [N][R] (not G)
   int64_t u0;
   int D, EF, R, C, KC, refine;
+  int stash;  // passes whose open pairs for the refinement are kept for later (all of them, or none)
 };
 
 template <int T>
@@ -181,7 +187,7 @@ __global__ __launch_bounds__(kPruneThreads, T <= 5 ? 4 : 2) void prune_kernel(Pr
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int D = a.D, R = a.R, C = a.C, KC = a.KC;
   const float* __restrict__ X = a.X;
-  const PruneLds L = prune_lds(C, R, KC);
+  const PruneLds L = prune_lds(C, R, KC, T, a.stash);
   _Float16* stage = reinterpret_cast<_Float16*>(sm + L.stage);
   uint32_t* occ = reinterpret_cast<uint32_t*>(sm + L.occ);
   double* cd = reinterpret_cast<double*>(sm + L.cd);
@@ -193,7 +199,9 @@ __global__ __launch_bounds__(kPruneThreads, T <= 5 ? 4 : 2) void prune_kernel(Pr
   uint32_t* queue = reinterpret_cast<uint32_t*>(sm + L.queue) + 128 * wave;
   int32_t* kept = reinterpret_cast<int32_t*>(sm + L.kept);  // R ids
   uint32_t* kbits = reinterpret_cast<uint32_t*>(kept + R);  // kept candidates, 32 a word (at most 34 words)
-  int32_t* scal = reinterpret_cast<int32_t*>(kbits + 64);   // [0] candidate count, [1] kept count
+  int32_t* scal = reinterpret_cast<int32_t*>(kbits + 64);   // [0] candidate count, [1] kept count, [2] the approximate
+                                                            // threshold, [3] some cosine is not approximated
+  uint32_t* stash = reinterpret_cast<uint32_t*>(sm + L.stash) + tid;
   unsigned long long* cstar = reinterpret_cast<unsigned long long*>(sm + L.queue);  // once the queues are empty
   const int64_t u = a.u0 + blockIdx.x;
   const float* xu = X + u * D;
@@ -215,7 +223,10 @@ __global__ __launch_bounds__(kPruneThreads, T <= 5 ? 4 : 2) void prune_kernel(Pr
       if (ok) si[n + lanes_below(m)] = v;
       n += __popcll(m);
     }
-    if (lane == 0) scal[0] = n;
+    if (lane == 0) {
+      scal[0] = n;
+      scal[3] = 0;
+    }
   }
   __syncthreads();
   {
@@ -387,6 +398,19 @@ __global__ __launch_bounds__(kPruneThreads, T <= 5 ? 4 : 2) void prune_kernel(Pr
   const int npairs = nt * (nt + 1) / 2;
   const int passes = (npairs + T * kPruneWaves - 1) / (T * kPruneWaves);
   const int per = passes ? (npairs + passes * kPruneWaves - 1) / (passes * kPruneWaves) : 0;  // tiles a wavefront holds
+  auto tiles_from = [&](int p0, int (&tile)[T]) {  // the T tiles from p0 on
+    int J = 0;
+    while ((J + 1) * (J + 2) / 2 <= p0) ++J;
+    int I = p0 - J * (J + 1) / 2;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      tile[t] = __builtin_amdgcn_readfirstlane(I | (J << 8));
+      if (++I > J) {
+        ++J;
+        I = 0;
+      }
+    }
+  };
   const int rowsh = KC == 64 ? 4 : KC == 32 ? 3 : 2;  // log2 of the lanes staging one row (four dimensions each)
   // place of a row's 16-byte slot s
   auto slot_of = [&](int s, int r) {
@@ -396,19 +420,7 @@ __global__ __launch_bounds__(kPruneThreads, T <= 5 ? 4 : 2) void prune_kernel(Pr
     const int p0 = (pass * kPruneWaves + wave) * per;
     const int mine = p0 >= npairs ? 0 : (npairs - p0 < per ? npairs - p0 : per);
     int tile[T];  // I | J << 8
-    {
-      int J = 0;
-      while ((J + 1) * (J + 2) / 2 <= p0) ++J;
-      int I = p0 - J * (J + 1) / 2;
-#pragma unroll
-      for (int t = 0; t < T; ++t) {
-        tile[t] = __builtin_amdgcn_readfirstlane(I | (J << 8));
-        if (++I > J) {
-          ++J;
-          I = 0;
-        }
-      }
-    }
+    tiles_from(p0, tile);
     float16v acc[T];
 #pragma unroll
     for (int t = 0; t < T; ++t)
@@ -479,6 +491,7 @@ __global__ __launch_bounds__(kPruneThreads, T <= 5 ? 4 : 2) void prune_kernel(Pr
             can = ballot(r * h >= 1e-6f * kUnitScale * kUnitScale);
             yes &= can;
             no &= can;
+            if ((pair & ~can) && lane == 0) scal[3] = 1;
           }
           word = lanes(1ull << i) ? (uint32_t)yes : word;
           word = lanes(1ull << (32 + i)) ? (uint32_t)(yes >> 32) : word;
@@ -489,6 +502,7 @@ __global__ __launch_bounds__(kPruneThreads, T <= 5 ? 4 : 2) void prune_kernel(Pr
         const int wr = 32 * I + 8 * ((lane & 15) >> 2) + 4 * half + (lane & 3);
         if ((lane & 31) < 16) occ[occ_row(wr) + J - I] = word;
         mask[t >> 1] |= open << (16 * (t & 1));
+        if (ballot(v < n && !(h < 3e38f)) && lane == 0) scal[3] = 1;
         if (a.refine && below > 0) atomicMax(&cmax[v], sortable32(cm));
       }
     if (a.refine) {
@@ -516,7 +530,14 @@ __global__ __launch_bounds__(kPruneThreads, T <= 5 ? 4 : 2) void prune_kernel(Pr
     }
     // the products are used up: their registers hold the rows of the exact sums
     drain(0, mask, tile);
-    if (a.refine) drain(1, maskb, tile);
+    if (a.refine) {
+      if (a.stash) {
+#pragma unroll
+        for (int t = 0; t < (T + 1) / 2; ++t) stash[kPruneThreads * (pass * ((T + 1) / 2) + t)] = maskb[t];
+      } else {
+        drain(1, maskb, tile);
+      }
+    }
   }
   __syncthreads();
 
@@ -547,8 +568,57 @@ __global__ __launch_bounds__(kPruneThreads, T <= 5 ? 4 : 2) void prune_kernel(Pr
   if (a.refine && nk < R) {
     // ---- refinement: the threshold is the need-th smallest t of the pruned
     const int np = n - nk, need = R - nk < np ? R - nk : np;
+    auto is_kept = [&](int i) { return (kbits[i >> 5] >> (i & 31)) & 1; };
+    if (a.stash) {
+      // The need-th smallest of the columns' approximate maxima is within
+      // kCosErr of the threshold, so a column further than twice that from it
+      // survives or does not whatever its exact value; the few others are
+      // computed.  (All are, where some cosine has no approximation.)
+      int32_t* exact = reinterpret_cast<int32_t*>(hv);  // the norms are used up
+      const bool all = scal[3] != 0;
+      for (int i = tid; i < nc; i += kPruneThreads)
+        if (i >= n || is_kept(i)) cmax[i] = 0x7fffffff;  // after every pruned one
+      __syncthreads();
+      for (int i = tid; i < n; i += kPruneThreads) {
+        const int x = cmax[i];
+        if (x == 0x7fffffff) continue;
+        int lt = 0, le = 0;
+        for (int j = 0; j < nc; j += 4) {
+          const int4 y = *reinterpret_cast<const int4*>(cmax + j);
+          lt += (y.x < x) + (y.y < x) + (y.z < x) + (y.w < x);
+          le += (y.x <= x) + (y.y <= x) + (y.z <= x) + (y.w <= x);
+        }
+        if (lt < need && need <= le) scal[2] = x;  // the same value from every lane that finds it
+      }
+      __syncthreads();
+      const float c = unsortable32(scal[2]), w = 2.0f * kCosErr * kUnitScale * kUnitScale;
+      for (int i = tid; i < nc; i += kPruneThreads) {
+        const bool pruned = i < n && !is_kept(i);
+        const float x = unsortable32(cmax[i]);
+        const bool lower = !all && x < c - w, upper = !all && x > c + w;
+        exact[i] = pruned && !lower && !upper;
+        if (pruned && lower) tv[i] = 0;
+        if (pruned && upper) tv[i] = ~1ull;
+      }
+      __syncthreads();
+      for (int pass = 0; pass < passes; ++pass) {
+        const int p0 = (pass * kPruneWaves + wave) * per;
+        const int mine = p0 >= npairs ? 0 : (npairs - p0 < per ? npairs - p0 : per);
+        int tile[T];
+        tiles_from(p0, tile);
+        uint32_t mask[(T + 1) / 2];
+#pragma unroll
+        for (int t = 0; t < (T + 1) / 2; ++t) mask[t] = stash[kPruneThreads * (pass * ((T + 1) / 2) + t)];
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+          if (t >= mine || !exact[t < mine ? 32 * (tile[t] >> 8) + (lane & 31) : 0])
+            mask[t >> 1] &= ~(0xffffu << (16 * (t & 1)));
+        drain(1, mask, tile);
+      }
+      __syncthreads();
+    }
     for (int i = tid; i < n; i += kPruneThreads)
-      if ((kbits[i >> 5] >> (i & 31)) & 1) tv[i] = ~0ull;  // kept: counts above every pruned one
+      if (is_kept(i)) tv[i] = ~0ull;  // kept: counts above every pruned one
     __syncthreads();
     for (int i = tid; i < n; i += kPruneThreads) {
       const unsigned long long x = tv[i];
@@ -692,16 +762,26 @@ hipError_t launch_prune(const float* X, int D, const int32_t* sids, int EF, cons
   if (nu <= 0) return hipSuccess;
   const int C = EF + R;  // EF results and R old neighbours
   if (D % 32 || D > 1024 || R > 64 || C > 32 * 34) return hipErrorInvalidValue;
-  // Chunks of 64 dimensions where they divide (half as many waits for the rows'
-  // loads as with 32; two workgroups of the five-tile kernel still fit a
-  // compute unit), fewer where the lists are so long that the LDS asks for it
-  int KC = D % 64 ? 32 : 64;
-  while (prune_lds(C, R, KC).total > 160 * 1024) KC >>= 1;
-  const size_t lds = (size_t)prune_lds(C, R, KC).total;
-  const PruneArgs a{X, N, sids, G, fill, Gout, u0, D, EF, R, C, KC, refine};
   // lists of up to 256 candidates are 36 tiles, 5 a wavefront: few enough
   // registers for two workgroups on a compute unit; longer lists hold 10 a
   // wavefront and go over the dimensions again for the tiles beyond 80
+  const int T = C <= 256 ? 5 : 10, nt = (C + 31) / 32;
+  const int passes = (nt * (nt + 1) / 2 + T * kPruneWaves - 1) / (T * kPruneWaves);
+  // Chunks of 64 dimensions where they divide (half as many waits for the rows'
+  // loads as with 32; two workgroups of the five-tile kernel still fit a
+  // compute unit), fewer where the lists are so long that the LDS asks for it;
+  // beyond that the refinement's pairs are computed pass by pass, not kept
+  int KC = D % 64 ? 32 : 64, stash = refine ? passes : 0;
+  while (prune_lds(C, R, KC, T, stash).total > 160 * 1024) {
+    if (KC > 32)
+      KC = 32;
+    else if (stash)
+      stash = 0;
+    else
+      KC = 16;
+  }
+  const size_t lds = (size_t)prune_lds(C, R, KC, T, stash).total;
+  const PruneArgs a{X, N, sids, G, fill, Gout, u0, D, EF, R, C, KC, refine, stash};
   auto go = [&](auto kern) {
     if (lds > 64 * 1024) {
       const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -711,7 +791,7 @@ hipError_t launch_prune(const float* X, int D, const int32_t* sids, int EF, cons
     hipLaunchKernelGGL(kern, dim3((unsigned)nu), dim3(kPruneThreads), lds, st, a);
     return hipGetLastError();
   };
-  return C <= 256 ? go(prune_kernel<5>) : go(prune_kernel<10>);
+  return T == 5 ? go(prune_kernel<5>) : go(prune_kernel<10>);
 }
 
 hipError_t launch_gather(const float* X, int D, const int32_t* ids, int64_t n, float* out, hipStream_t st) {
