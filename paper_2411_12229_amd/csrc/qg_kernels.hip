@@ -2001,20 +2001,27 @@ __device__ bool search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
 }
 
 // Minimum wavefronts per SIMD the register allocator must allow (1: no
-// constraint).  Beams of three and four registers at D <= 256: 4 (LDS allows
-// hardly more; at 6 they spill 100-190 bytes); of six and eight: 3.  LDS-beam kernels with D <= 256: 6 for the stop-only and
-// mixed-batch modes.  Register-beam kernels with R = 32, plain or mixed
-// batches, D = 128 (but the one-word plain kernel, which fits in 80 registers
-// anyway) and D = 96: 6, where the allocator would otherwise take 82-96
+// constraint).
+// D <= 256, beam in LDS: 6 for the stop-only and mixed-batch modes.  Beam in
+// one or two registers, R = 32: 6 where the allocator would otherwise take 82-96
 // registers and drop to 5 wavefronts per SIMD; the few values it then keeps in
-// scratch (16-56 bytes per lane) cost less than the lost wavefront (5-17%
-// faster at 10,000 and 80,000 queries).  The stop kernels with the beam in
-// registers at D = 128, R = 32 (one query or a mixed batch): 6 as well (107-115
-// registers and 4 wavefronts otherwise; 48-84 bytes of scratch; 6-16% faster).  Measured not to pay: 4 for D = 768 (32
-// bytes of scratch, 1-2% slower); R = 64 would spill over 100 bytes.
+// scratch cost less than the lost wavefront (plain and mixed 5-17% faster at
+// 10,000 and 80,000 queries, the stop kernels at D = 128 6-16%).  Beams of three
+// and four registers: 4 (LDS allows hardly more; at 6 they spill 100-190
+// bytes); of six and eight: 3.
+// D > 256, plain and mixed modes: 3, which costs the shapes of 170-205
+// registers 4-40 spilled values and gains a third wavefront: 960 x 64 at 3,000
+// queries, ef 48 440 against 385 us, ef 192 1,056 against 865 us, at 10,000
+// 1,148 against 1,079 us; 960 x 32, ef 300, 10,000 queries 4,275 against 3,362
+// us; nothing lost at 1,000.  Not for six registers at 960 x 64 (848 against
+// 1,029 us at 1,000 queries), nor with the stop, whose LDS sets the residency.
+// Measured not to pay: 4 for D = 768, R = 32 (4% faster at 10,000 queries, 2-4%
+// slower at 3,000 and 5,000).
 template <int D, int R, int LS, int NB, bool INL>
 constexpr int waves_hint() {
   if constexpr (INL) return 1;  // few queries: nothing to be resident beside
+  if constexpr (D > 256 && (LS == kLsOff || LS == kMixed) && NB > 0 && NB <= 6 && !(NB == 6 && D == 960 && R == 64))
+    return 3;
   if constexpr (NB > 4) return D <= 256 ? 3 : 1;
   if constexpr (NB > 2) return D <= 256 ? 4 : 1;
   if constexpr (NB > 0) {
