@@ -107,3 +107,35 @@ def test_stop_equals_oracle(made, D, R, k, ef):
                                             stats=True)
         assert np.array_equal(ids.cpu().numpy(), oi) and np.array_equal(dists.cpu().numpy(), od)
         assert np.array_equal(st.cpu().numpy()[:, :3], os_[:, :3])
+
+
+@pytest.mark.parametrize("nq", [1, 40, 90])
+def test_captured_searches_replay(made, nq):
+    """Small batches (one search launch) and larger ones (with the overflow pass) recorded into a graph, replayed
+    between eager calls; some queries outgrow the on-chip visited set."""
+    idx, blocks, M, e, Q = made(96, 32)
+    q = T(np.concatenate([Q] * 3)[:nq])
+    flags = qg.QG_SEARCH_SMALL_HASH
+    want = idx.search(q, 10, 130, flags=flags)
+    torch.cuda.synchronize()
+    s = torch.cuda.Stream()
+    ids = torch.empty((nq, 10), dtype=torch.int32, device=DEV)
+    dists = torch.empty((nq, 10), dtype=torch.float32, device=DEV)
+    g = torch.cuda.CUDAGraph()
+    try:
+        with torch.cuda.graph(g, stream=s):
+            idx.set_stream(torch.cuda.current_stream())
+            qg.qg_search_ex(idx, q, nq, 10, 130, flags, ids, dists)
+        idx.set_stream(None)
+        for _ in range(4):
+            ids.fill_(-7)
+            dists.zero_()
+            torch.cuda.synchronize()
+            g.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(ids, want[0]) and torch.equal(dists, want[1])
+            again = idx.search(q, 10, 130, flags=flags)
+            torch.cuda.synchronize()
+            assert torch.equal(again[0], want[0])
+    finally:
+        idx.set_stream(None)
