@@ -80,7 +80,7 @@ struct qg_index {
   int64_t fb_words = 0;
   // launch shape chosen by qg_autotune: wavefronts per workgroup (preferred,
   // halved while the LDS does not fit) and visited-hash slots per beam entry
-  int wpb_pref = 4;
+  int wpb_pref = 0;  // 0: by the batch (waves_per_group)
   int hash_factor = 3;
   int cu_waves = 0;  // cap on resident wavefronts per compute unit (0 = as many as fit)
   int cus = 256;     // compute units of the device (read at creation; sizes the persistent grid)
@@ -499,6 +499,24 @@ struct FixedScratch {
   int* counters;
 };
 
+// Wavefronts per workgroup where no shape has been set, and always with the
+// stop's network in LDS.  A batch of at most two queries a compute unit runs one
+// wavefront a workgroup: the dispatcher then gives each query a compute unit of
+// its own while there are any, with its LDS and its path to memory (4 against 1
+// wavefronts: 960 x 64, ef 128, 37 queries 334 against 323 us; 128 x 32, ef 192,
+// 128 queries 280 against 268; 500 queries 298 against 293; 1,000 equal).
+// Larger ones run 4.  With the network, staged once a workgroup (10.6 KB): 8,
+// which it had at every size, costs residency, 768 x 32, ef 96, 10,000 queries
+// 1,085 against 893 us with 4, and leaves compute units without a workgroup (960
+// x 64, ef 64, 256 queries 265 against 229 us with 1, 1,000 queries 296 against
+// 265 with 4), except where eights give every unit just one (128 x 32, ef 48,
+// 2,000 queries 122 against 128 us with 4).  A few queries stage it with four
+// (one query, 768 x 32 174 against 171 us, 128 x 32 equal).
+static int waves_per_group(int64_t nq, int64_t cus, bool mlp_lds) {
+  if (nq <= 2 * cus) return mlp_lds && nq < 8 ? 4 : 1;
+  return mlp_lds && nq > 4 * cus && nq <= 8 * cus ? 8 : 4;
+}
+
 // Every search entry point ends here.  k and ef are the values of a uniform
 // batch, or the bounds of a mixed one (k_q, ef_q: per-query device arrays).
 // With fx, nothing is allocated: the rotated queries, overflow list and queue
@@ -604,7 +622,7 @@ static int search_impl(const qg_index* cidx, const float* queries, int64_t nq, i
   const size_t lds_cap = 160 * 1024;
   const bool mlp_lds = ls == 1 || ls == 4;
   const size_t extra = mlp_lds ? qgk::mlp_lds_bytes() : 0;  // MLP image shared by a workgroup
-  int wpb = mlp_lds ? 8 : idx->wpb_pref;  // 8 wavefronts share the MLP image
+  int wpb = mlp_lds || !idx->wpb_pref ? waves_per_group(nq, idx->cus, mlp_lds) : idx->wpb_pref;
   while (wpb > 1 && (size_t)wpb * L.total + extra > lds_cap) wpb >>= 1;
   if ((size_t)L.total + extra > lds_cap) return fail(QG_EUNSUPPORTED, "per-query LDS exceeds the device limit");
   const size_t lds = (size_t)wpb * L.total + extra;

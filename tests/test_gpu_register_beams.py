@@ -139,3 +139,33 @@ def test_captured_searches_replay(made, nq):
             assert torch.equal(again[0], want[0])
     finally:
         idx.set_stream(None)
+
+
+@pytest.mark.parametrize("mode", ["plain", "mixed", "stop", "mixed stop"])
+def test_batch_sizes_agree(made, mode):
+    """The workgroup's size follows the batch's: around each change (with 256 compute units) every row is the
+    oracle's."""
+    D, R, k, ef = 96, 32, 10, 40
+    idx, blocks, M, e, Q = made(D, R)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    rng = np.random.Generator(np.random.PCG64(5))
+    mlp = torch.from_numpy(0.1 * rng.standard_normal(qg.QG_STOP_MLP_PARAMS)).to(torch.bfloat16).view(torch.int16)
+    stop = dict(theta=0.0, t_min=4, t_every=3)
+    if "stop" in mode:
+        o = oracle.search_ls(blocks, D, R, e, M, Q, k, ef, w=mlp.numpy().view(np.uint16), **stop)
+    else:
+        o = oracle.search(blocks, D, R, e, M, Q, k, ef)
+    for nq in (7, 8, cus, 2 * cus, 2 * cus + 1, 4 * cus, 4 * cus + 1, 8 * cus, 8 * cus + 1):
+        pick = np.arange(nq) % len(Q)
+        q = T(Q[pick])
+        ks, efs = (torch.full((nq,), v, dtype=torch.int32, device=DEV) for v in (k, ef))
+        print(f"{mode} nq={nq}", flush=True)
+        if mode == "plain":
+            got = idx.search(q, k, ef)
+        elif mode == "mixed":
+            got = idx.search_mixed(q, ks, efs, k_max=k, ef_max=ef)
+        elif mode == "stop":
+            got = idx.search_stop(q, k, ef, mlp.to(DEV), **stop)
+        else:
+            got = idx.search_mixed_stop(q, ks, efs, mlp.to(DEV), k_max=k, ef_max=ef, **stop)
+        assert np.array_equal(got[0].cpu().numpy(), o[0][pick]) and np.array_equal(got[1].cpu().numpy(), o[1][pick])
