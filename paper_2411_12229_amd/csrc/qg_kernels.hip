@@ -2007,8 +2007,13 @@ __device__ bool search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
 // registers and drop to 5 wavefronts per SIMD; the few values it then keeps in
 // scratch cost less than the lost wavefront (plain and mixed 5-17% faster at
 // 10,000 and 80,000 queries, the stop kernels at D = 128 6-16%).  Beams of three
-// and four registers: 4 (LDS allows hardly more; at 6 they spill 100-190
-// bytes); of six and eight: 3.
+// and four registers: plain 5 (at most 28 bytes of scratch; 4 against 5, 128 x
+// 32, ef 200, k 200: 3,000 queries 485 against 478 us, 5,000 726 against 618,
+// 10,000 1,130 against 1,084, 60,000 5,480 against 4,982), but 4 for 128 x 64
+// (10-13 spilled values, 3,000 queries 411 against 428 us), for mixed batches,
+// whose few long queries then share a SIMD with more others (96 x 32, ef up to
+// 192, 5,000 queries 497 against 544 us) and with the stop; at 6 they spill
+// 100-190 bytes.  Of six and eight: 3.
 // D > 256, plain and mixed modes: 3, which costs the shapes of 170-205
 // registers 4-40 spilled values and gains a third wavefront: 960 x 64 at 3,000
 // queries, ef 48 440 against 385 us, ef 192 1,056 against 865 us, at 10,000
@@ -2023,7 +2028,7 @@ constexpr int waves_hint() {
   if constexpr (D > 256 && (LS == kLsOff || LS == kMixed) && NB > 0 && NB <= 6 && !(NB == 6 && D == 960 && R == 64))
     return 3;
   if constexpr (NB > 4) return D <= 256 ? 3 : 1;
-  if constexpr (NB > 2) return D <= 256 ? 4 : 1;
+  if constexpr (NB > 2) return D > 256 ? 1 : LS == kLsOff && !(D == 128 && R == 64) ? 5 : 4;
   if constexpr (NB > 0) {
     constexpr bool mode = LS == kLsOff || LS == kMixed;
     if constexpr (R == 32 && D == 128 && (LS == kLsStop || LS == kMixedStop)) return 6;
@@ -2039,7 +2044,7 @@ constexpr int waves_hint() {
 // GV = false: main pass over all queries with the LDS visited hash.
 // GV = true : overflow pass over the queries the main pass handed over, with
 //             a global bitset per wavefront.
-// The stop-only kernels share one MLP image per workgroup of 8 wavefronts.
+// The stop-only kernels share one MLP image per workgroup.
 // For the narrow shapes the stop-only and mixed-batch kernels hold their
 // registers to 80, so that 6 wavefronts per SIMD fit (LDS sets residency for
 // the stop-only kernels anyway).
