@@ -2006,7 +2006,12 @@ __device__ bool search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
 // one or two registers, R = 32: 6 where the allocator would otherwise take 82-96
 // registers and drop to 5 wavefronts per SIMD; the few values it then keeps in
 // scratch cost less than the lost wavefront (plain and mixed 5-17% faster at
-// 10,000 and 80,000 queries, the stop kernels at D = 128 6-16%).  Beams of three
+// 10,000 and 80,000 queries, the stop kernels at D = 128 6-16%).  128 x 64, plain: 5
+// (two registers took 98, two too many, and spill nothing at 96: ef 96, 3,000
+// queries equal, 6,000 269 against 256 us, 60,000 1,791 against 1,637).  Not for
+// R = 64 with mixed batches, for any stop but 128 x 32's, nor 6 for 96 x 64:
+// 3-10% faster from 6,000 queries on, but 1-5% slower below 4,500, by what they
+// spill.  Beams of three
 // and four registers: plain 5 (at most 28 bytes of scratch; 4 against 5, 128 x
 // 32, ef 200, k 200: 3,000 queries 485 against 478 us, 5,000 726 against 618,
 // 10,000 1,130 against 1,084, 60,000 5,480 against 4,982), but 4 for 128 x 64
@@ -2034,6 +2039,7 @@ constexpr int waves_hint() {
     if constexpr (R == 32 && D == 128 && (LS == kLsStop || LS == kMixedStop)) return 6;
     if constexpr (R == 32 && D == 128) return mode ? 6 : 1;
     if constexpr (R == 32 && D == 96) return mode ? 6 : 1;
+    if constexpr (R == 64 && D == 128) return LS == kLsOff ? 5 : 1;
     return 1;
   }
   return D > 256 ? 1 : (mlp_in_lds<LS> || LS == kMixed) ? 6 : 1;
