@@ -60,6 +60,12 @@ constexpr int kPruneThreads = 64 * kPruneWaves;
 // for D <= 1024.  Sum 1.11e-3.
 constexpr float kCosErr = 1.25e-3f;
 constexpr float kUnitScale = 4096.0f;                        // f16 elements hold 2^12 times the unit vector's
+// Smallest norm, relative to the largest, of a vector that is approximated: the
+// factors 2^12 / norm and 2^23 / norm (which scales the limits, and times norms
+// of at most 1 also the limits) then stay below 2^124 in fp32.  A shorter one,
+// zero and NaN among them, gets NaN for a factor, and with it NaN products and
+// limits: no comparison with them holds, so its pairs are left open.
+constexpr double kMinNorm = 0x1p-100;
 
 // Dynamic LDS of prune_kernel (bytes).  stage: the f16 rows of one chunk of KC
 // dimensions, and before that the sort; occ: row w's bits over the 32-blocks
@@ -332,7 +338,7 @@ __global__ __launch_bounds__(kPruneThreads, T <= 5 ? 4 : 2) void prune_kernel(Pr
     cd[i] = d;
     id[i] = live ? si[i] : 0;
     rw[i] = (float)r;
-    hv[i] = live ? 0.5f / (float)r : 0.0f;
+    hv[i] = live ? (r >= kMinNorm ? 0.5f / (float)r : __builtin_nanf("")) : 0.0f;
     cmax[i] = sortable32(-2.0f * kUnitScale * kUnitScale);
     tv[i] = sortable64(-2.0);
   }
@@ -461,9 +467,9 @@ __global__ __launch_bounds__(kPruneThreads, T <= 5 ? 4 : 2) void prune_kernel(Pr
     }
     // lane l holds column v = 32 J + l % 32, rows w = 32 I + 8 (i / 4) + 4 (l / 32) + i % 4
     // The comparisons are made on the products as they are, against limits
-    // scaled alike.  A pair whose |w - u| is lost beside |v - u|, or with a
-    // norm of zero or beyond fp32, is left open (the limits are not ordered
-    // for NaN); that is looked for once a tile, in its first row, which has the
+    // scaled alike.  A pair with a norm below kMinNorm has a NaN product, and is
+    // left open by every comparison.  So is one whose |w - u| is lost beside
+    // |v - u|; that is looked for once a tile, in its first row, which has the
     // smallest |w - u|.
     uint32_t mask[(T + 1) / 2], maskb[(T + 1) / 2];
 #pragma unroll
