@@ -2297,9 +2297,14 @@ hipError_t launch_rotate(const float* in, int64_t n, int D, const float* M, floa
   // of products over the SIMDs, so weighed, decide as measured (one tile / 2 x
   // 2): 37 x 960 18 / 40 us, 1,000 x 768 35 / 38, 1,000 x 960 51 / 47, 10,000 x
   // 128 13.6 / 15.1, 20,011 x 128 21.7 / 20.5, 10,000 x 768 238 / 202.
-  auto rounds = [](int64_t tiles) { return (tiles + 1023) / 1024; };
+  // A last round of single tiles that is less than a quarter full costs little,
+  // one more than that a whole one: wide rows take two rounds of blocks from 5.25
+  // rounds of tiles on (1,400 x 960, 5.16 rounds, 62 / 68; 1,500 x 960, 5.5, 70 /
+  // 68; 1,700 x 768, 5.02, 50 / 55; 2,000 x 768, 5.86, 58 / 55).
   const int64_t t1 = (n + 15) / 16 * (D / 16), t2 = (n + 31) / 32 * (D / 32);
-  const bool two = v4 && D % 32 == 0 && 4.0 * (double)rounds(t2) <= 1.2 * (double)rounds(t1);
+  const int64_t r1 = (t1 + 1023) / 1024, r2 = (t2 + 1023) / 1024;
+  const bool fewer = 4.0 * (double)r2 <= 1.2 * (double)r1 || (D > 256 && r2 == 2 && 4 * t1 > 21 * 1024);
+  const bool two = v4 && D % 32 == 0 && fewer;
   const int nt = two ? 2 : 1;
   const int64_t blocks = (n + 16 * nt - 1) / (16 * nt);  // row blocks, padded to a multiple of 8 (one per XCD)
   const dim3 grid((unsigned)(((blocks + 7) / 8) * 8 * (D / (16 * nt))));
