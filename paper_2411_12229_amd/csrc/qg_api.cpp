@@ -623,6 +623,21 @@ static int search_impl(const qg_index* cidx, const float* queries, int64_t nq, i
   const bool mlp_lds = ls == 1 || ls == 4;
   const size_t extra = mlp_lds ? qgk::mlp_lds_bytes() : 0;  // MLP image shared by a workgroup
   int wpb = mlp_lds || !idx->wpb_pref ? waves_per_group(nq, idx->cus, mlp_lds) : idx->wpb_pref;
+  // With the stop and more queries than that rule measured: eight where they hold
+  // more wavefronts than four, for then the LDS sets residency and the network's
+  // share of it is halved.  For beams in LDS (128 x 32, ef 300, 10,000 queries 894
+  // us with four, 770 with eight; 96 x 64, ef 384, 30,000 2,828 against 2,310; 768 x
+  // 32, ef 700, 10,000 3,355 against 2,005), and for four registers from three
+  // queries a SIMD on (128 x 32, ef 256, 30,000 1,712 against 1,469, 3,500 366
+  // against 352, but 2,500 313 against 342).  Fewer registers lost 3-11% at 2,500 to
+  // 5,000 queries (ef 100), more have no such batches or the same residency.
+  if (mlp_lds && (nb == 0 ? nq > 8LL * idx->cus : nb == 4 && nq > 12LL * idx->cus)) {
+    auto resident = [&](int w) {
+      const size_t l = (size_t)w * L.total + extra;
+      return l > lds_cap ? 0 : w * qgk::search_occupancy(idx->D, idx->R, qgk::kMainPass, ls, nb, lb, w, l);
+    };
+    wpb = resident(8) > resident(4) ? 8 : 4;
+  }
   while (wpb > 1 && (size_t)wpb * L.total + extra > lds_cap) wpb >>= 1;
   if ((size_t)L.total + extra > lds_cap) return fail(QG_EUNSUPPORTED, "per-query LDS exceeds the device limit");
   const size_t lds = (size_t)wpb * L.total + extra;
