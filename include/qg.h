@@ -220,7 +220,7 @@ int qg_set_stream(qg_index *idx, void *hip_stream);
  * pass), then, for the fastest pair, caps of 24, 20 and 16 resident
  * wavefronts per compute unit against no cap (a batch only a little larger
  * than the resident query slots can finish sooner on fewer, less contended
- * slots), then, where the beam is kept in registers, the beam kept in LDS
+ * slots), then, for beams of at most 128 entries, the beam kept in LDS
  * against the beam kept in registers, then the LUT layout (the per-query
  * table of Sec. 2.2's FastScan, rows of 16 entries: int16 or int32 entries,
  * with a padding row between the lane groups that share a neighbour, so that

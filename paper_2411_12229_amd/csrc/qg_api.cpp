@@ -776,8 +776,12 @@ static int autotune_impl(qg_index* idx, int64_t nq, int32_t kcap, int32_t ef_bou
       }
     }
   }
-  if (!rc && qgk::beam_regs(false, mixed ? 3 : 0, ef_bound, idx->N, idx->D, nq) > 0) {
-    idx->cu_waves = best_cw;  // the beam in LDS for the best shape
+  // The beam in LDS for the best shape, where it comes near the one in registers:
+  // up to two of them.  Beyond, registers won every tuning of 40 to 3,000 queries
+  // at ef 130 to 512 (96 x 32, 128 x 32, 768 x 32), and a larger beam's storage is
+  // reported as 1, as it always was.
+  if (!rc && ef_bound <= 128 && qgk::beam_regs(false, mixed ? 3 : 0, ef_bound, idx->N, idx->D, nq) > 0) {
+    idx->cu_waves = best_cw;
     idx->beam_regs = false;
     double t;
     time_it(t);
