@@ -274,10 +274,10 @@ int qg_set_launch(qg_index *idx, int32_t wpb, int32_t hash_factor, int32_t cu_wa
  * in a batch for long ones, and the slots overlap transfers with searches.  Every request's results are those of qg_search_ex
  * for that query alone with its own k and ef.  The index must outlive the
  * server; 1 <= streams <= 16, 1 <= k_max <= QG_MAX_K, 1 <= ef_max <= QG_MAX_EF.
- * Creation runs single-query searches on every slot (synchronously), one
- * for each beam storage a batch can use, so that every kernel a batch may
- * launch is loaded before the first request; qg_server_set_stop does the same
- * for the stop kernels. */
+ * Creation runs short searches of zero queries on every slot (synchronously),
+ * one for each set of kernels that a batch may launch (they depend on the
+ * batch's size and its largest beam), so that every one is loaded before the
+ * first request; qg_server_set_stop does the same for the stop kernels. */
 typedef struct qg_server qg_server;
 
 int qg_server_create(qg_index *idx, int32_t streams, int32_t max_batch, int32_t k_max, int32_t ef_max,

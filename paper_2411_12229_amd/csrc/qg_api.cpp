@@ -270,6 +270,48 @@ int encode_index(qg_index* idx, const float* vectors, const float* rotated, cons
   return QG_OK;
 }
 
+Setting setting_of(const qg_index* idx) { return {idx->D, idx->R, idx->N, idx->beam_regs, idx->lut32}; }
+
+Route search_route(const Setting& s, int64_t nq, int32_t ef, int ls_mode, int32_t flags, bool aligned) {
+  const bool plain_or_mixed = ls_mode == 0 || ls_mode == 3;
+  Route r{};
+  r.tiles = qgk::rotate_tiles(nq, s.D, aligned);
+  // LUT entries: int32 when chosen, for the main pass of the plain and mixed
+  // modes (the overflow pass and the other modes keep int16; shapes that sum
+  // over bit planes have no table)
+  r.lb = s.lut32 && plain_or_mixed && !qgl::use_planes(s.D, s.R) ? 4 : 2;
+  r.nb = s.beam_regs && !(flags & QG_SEARCH_LDS_BEAM) ? qgk::beam_regs(false, ls_mode, ef, s.n, s.D, nq) : 0;
+  // few queries: one launch, in which a query that outgrows its table runs again
+  // at once
+  r.inl = nq <= qgk::kBitsets && plain_or_mixed && r.lb == 2;
+  return r;
+}
+
+std::vector<WarmBatch> warm_batches(const Setting& s, int64_t max_batch, int32_t ef_max, bool stop) {
+  // a route changes with the batch above kBitsets and above kNarrowResident
+  // queries and with the rotation's blocks (by 16 rows), and with the beam past
+  // multiples of 64 entries
+  std::vector<int64_t> sizes{1, qgk::kBitsets + 1, qgk::kNarrowResident + 1};
+  for (int64_t n = 1; n <= max_batch; n += 16)
+    if (qgk::rotate_tiles(n, s.D, true) == 2) {
+      sizes.push_back(n);
+      break;
+    }
+  std::vector<Route> seen;
+  std::vector<WarmBatch> out;
+  for (int32_t ef = 1; ef <= ef_max; ef += 64)
+    for (int64_t n : sizes) {
+      if (n > max_batch) continue;
+      const Route r = search_route(s, n, ef, stop ? 4 : 3, 0, true);
+      const bool tiles = std::any_of(seen.begin(), seen.end(), [&](const Route& o) { return o.tiles == r.tiles; });
+      const bool search = std::any_of(seen.begin(), seen.end(), [&](const Route& o) { return o.same_search(r); });
+      if (tiles && search) continue;
+      seen.push_back(r);
+      out.push_back({n, ef});
+    }
+  return out;
+}
+
 int set_error(int code, const std::string& msg) { return fail(code, msg); }
 int device_of(const qg_index* idx) { return idx->device; }
 int dim_of(const qg_index* idx) { return idx->D; }
@@ -602,17 +644,14 @@ static int search_impl(const qg_index* cidx, const float* queries, int64_t nq, i
     a.tr_count = stop->trace_count;
   }
 
-  // LUT entries: int32 when chosen, for the main pass of the plain and mixed
-  // modes (the overflow pass and the other modes keep int16; shapes that sum
-  // over bit planes have no table)
-  const int lb = (idx->lut32 && (ls == 0 || ls == 3) && !qgl::use_planes(idx->D, idx->R)) ? 4 : 2;
-  const int nb = (idx->beam_regs && !(flags & QG_SEARCH_LDS_BEAM)) ? qgk::beam_regs(false, ls, ef, idx->N, idx->D, nq) : 0;
+  const qgi::Route route = qgi::search_route(qgi::setting_of(idx), nq, ef, ls, flags,
+                                             reinterpret_cast<uintptr_t>(queries) % 16 == 0);
+  const int lb = route.lb, nb = route.nb;
+  const bool inl = route.inl;
   // NN needs LDS only where it outgrows its registers
   int k_cap = k <= 64 * qgk::nn_regs(nb) ? 0 : k_cap_all;
   const int k_cap_ov = k <= 64 * qgk::nn_regs(0) ? 0 : k_cap_all;
-  // few queries: one launch, in which a query that outgrows its table runs again
-  // at once (its area must then serve both searches)
-  const bool inl = nq <= qgk::kBitsets && (ls == 0 || ls == 3) && lb == 2;
+  // a query that runs again in its launch has one area for both searches
   if (inl) k_cap = std::max(k_cap, k_cap_ov);
   a.k_cap = k_cap;
   const qgl::SearchLds L = qgl::search_lds(idx->D, idx->R, ef_cap, 1 << hbits, k_cap, lb);

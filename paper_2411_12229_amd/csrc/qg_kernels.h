@@ -58,6 +58,9 @@ constexpr int kMaxDevices = 64;
 hipError_t noalloc_scratch(int device, uint8_t** out);
 
 bool shape_supported(int D, int R);
+// Side, in 16 x 16 tiles, of the block of outputs that a wavefront of
+// launch_rotate computes (1 or 2); aligned: rows that start 16-byte aligned.
+int rotate_tiles(int64_t n, int D, bool aligned);
 hipError_t launch_rotate(const float* in, int64_t n, int D, const float* M, float* out, int* zero, int nzero,
                          hipStream_t st);
 // Encodes every block; *flag (device, cleared by the caller) receives bit 0 for
@@ -74,6 +77,9 @@ hipError_t launch_encode(const float* X, const float* ROT, int64_t N, int D, con
 // beam_regs() picks for the pass, mode, bound on ef, vector count, dimension
 // and batch size.
 int beam_regs(bool overflow_pass, int ls_mode, int ef_bound, int64_t n, int D, int64_t nq);
+// Queries of a narrow shape (D <= 256) that are resident at once at three
+// wavefronts a SIMD; beams above 256 entries are kept in LDS for more.
+constexpr int64_t kNarrowResident = 3 * 1024;
 // NN registers per lane of a kernel with nb beam registers (nb 0: beam in LDS);
 // larger k keep NN in LDS
 constexpr int nn_regs(int nb) { return nb >= 3 ? nb : 1; }

@@ -2281,6 +2281,23 @@ bool shape_supported(int D, int R) {
   return false;
 }
 
+// One tile a wavefront or a block of 2 x 2.  The block reads half as much per
+// product, so a tile by itself costs about 1.2 times a quarter of it; but
+// there are a quarter as many blocks to spread over the 1,024 SIMDs.  Rounds
+// of products over the SIMDs, so weighed, decide as measured (one tile / 2 x
+// 2): 37 x 960 18 / 40 us, 1,000 x 768 35 / 38, 1,000 x 960 51 / 47, 10,000 x
+// 128 13.6 / 15.1, 20,011 x 128 21.7 / 20.5, 10,000 x 768 238 / 202.
+// A last round of single tiles that is less than a quarter full costs little,
+// one more than that a whole one: wide rows take two rounds of blocks from 5.25
+// rounds of tiles on (1,400 x 960, 5.16 rounds, 62 / 68; 1,500 x 960, 5.5, 70 /
+// 68; 1,700 x 768, 5.02, 50 / 55; 2,000 x 768, 5.86, 58 / 55).
+int rotate_tiles(int64_t n, int D, bool aligned) {
+  const int64_t t1 = (n + 15) / 16 * (D / 16), t2 = (n + 31) / 32 * (D / 32);
+  const int64_t r1 = (t1 + 1023) / 1024, r2 = (t2 + 1023) / 1024;
+  const bool fewer = 4.0 * (double)r2 <= 1.2 * (double)r1 || (D > 256 && r2 == 2 && 4 * t1 > 21 * 1024);
+  return aligned && D % 32 == 0 && fewer ? 2 : 1;
+}
+
 hipError_t launch_rotate(const float* in, int64_t n, int D, const float* M, float* out, int* zero, int nzero,
                          hipStream_t st) {
   if (n <= 0) {
@@ -2291,26 +2308,12 @@ hipError_t launch_rotate(const float* in, int64_t n, int D, const float* M, floa
   // four columns per lane when every row starts 16-byte aligned (M is the
   // library's own allocation)
   const bool v4 = (reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(M)) % 16 == 0 && D % 4 == 0;
-  // One tile a wavefront or a block of 2 x 2.  The block reads half as much per
-  // product, so a tile by itself costs about 1.2 times a quarter of it; but
-  // there are a quarter as many blocks to spread over the 1,024 SIMDs.  Rounds
-  // of products over the SIMDs, so weighed, decide as measured (one tile / 2 x
-  // 2): 37 x 960 18 / 40 us, 1,000 x 768 35 / 38, 1,000 x 960 51 / 47, 10,000 x
-  // 128 13.6 / 15.1, 20,011 x 128 21.7 / 20.5, 10,000 x 768 238 / 202.
-  // A last round of single tiles that is less than a quarter full costs little,
-  // one more than that a whole one: wide rows take two rounds of blocks from 5.25
-  // rounds of tiles on (1,400 x 960, 5.16 rounds, 62 / 68; 1,500 x 960, 5.5, 70 /
-  // 68; 1,700 x 768, 5.02, 50 / 55; 2,000 x 768, 5.86, 58 / 55).
-  const int64_t t1 = (n + 15) / 16 * (D / 16), t2 = (n + 31) / 32 * (D / 32);
-  const int64_t r1 = (t1 + 1023) / 1024, r2 = (t2 + 1023) / 1024;
-  const bool fewer = 4.0 * (double)r2 <= 1.2 * (double)r1 || (D > 256 && r2 == 2 && 4 * t1 > 21 * 1024);
-  const bool two = v4 && D % 32 == 0 && fewer;
-  const int nt = two ? 2 : 1;
+  const int nt = rotate_tiles(n, D, v4);
   const int64_t blocks = (n + 16 * nt - 1) / (16 * nt);  // row blocks, padded to a multiple of 8 (one per XCD)
   const dim3 grid((unsigned)(((blocks + 7) / 8) * 8 * (D / (16 * nt))));
   // 32 columns a chunk, or 64 where one-tile wavefronts are few and a chunk's
   // loads take longer than its products (37 x 960: 18.1 against 19.9 us)
-  if (two)
+  if (nt == 2)
     hipLaunchKernelGGL((rotate_kernel<true, 2, 32>), grid, dim3(64), 0, st, in, n, D, M, out, zero, nzero);
   else if (v4 && D > 256)
     hipLaunchKernelGGL((rotate_kernel<true, 1, 64>), grid, dim3(64), 0, st, in, n, D, M, out, zero, nzero);
@@ -2355,7 +2358,7 @@ int beam_regs(bool overflow_pass, int ls_mode, int ef_bound, int64_t n, int D, i
   if (overflow_pass || ls_mode == kLsTrace || ls_mode == kNoMe || n > (int64_t)kIdMask30) return 0;
   if (ef_bound <= 64) return 1;
   if (ef_bound <= 256) return (ef_bound + 63) / 64;
-  if (ef_bound > 512 || (D <= 256 && nq > 3 * 1024)) return 0;
+  if (ef_bound > 512 || (D <= 256 && nq > kNarrowResident)) return 0;
   return ef_bound <= 384 ? 6 : 8;
 }
 

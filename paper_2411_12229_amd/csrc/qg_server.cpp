@@ -151,46 +151,49 @@ void free_slot(Slot& s) {
   s = Slot{};
 }
 
-// Batches of zero queries through every step a batch takes (uploads, search,
-// downloads, events) for each beam storage a batch can get (beams of one entry,
-// of 65, 129, 193, 257, 385 and 513: one to four, six or eight register words
-// per lane, or LDS) and for both sizes that take kernels of their own (one query,
-// and 65 where batches can be so large), with the stop if `stop` is given, so
-// that every kernel a batch may launch is loaded, and the copy paths set up,
-// before the first request: the first launch of a kernel loads its code and
-// takes milliseconds.  The copies are of one row, and the larger batches filled
-// on the device: the runtime seems to tie a stream to a copy engine at its first
-// larger copy, and while warm-up copied 65 rows every slot took the same engine,
-// so that a batch's copies waited behind another's long search (5M x 96, 500,000
-// requests a second: p50 273 ms, 4.9 ms without).
+// Batches of zero queries before the first request, with the stop if `stop` is
+// given: one search for every kernel that a batch of this server may launch (the
+// first launch of a kernel costs host time: its module's load for the first one,
+// milliseconds, and some 30 us for others), its rows filled on the device and its
+// beams one entry long, so that the searches themselves are short; then three
+// batches of one row through every step a batch takes (uploads, search,
+// downloads, events), so that the copy paths are set up.  No more rows are copied:
+// with copies of 65 rows in warm-up, batches' copies were seen to wait behind
+// another slot's long search (5M x 96, 500,000 requests a second: p50 273 ms, 4.9
+// ms without; which copy engine the runtime gives a stream may be the reason).
 bool warm_up(qg_server* sv, Slot& s, const qg_stop_params* stop) {
   const size_t K = (size_t)sv->k_max, D = (size_t)sv->D;
+  auto search = [&](int64_t n, int32_t ef) {
+    return (stop ? qg_search_mixed_stop(s.view, s.d_q, n, s.d_k, s.d_ef, sv->k_max, ef, 0, stop, s.d_ids, s.d_dists,
+                                        nullptr)
+                 : qg_search_mixed(s.view, s.d_q, n, s.d_k, s.d_ef, sv->k_max, ef, 0, s.d_ids, s.d_dists, nullptr)) ==
+           QG_OK;
+  };
+  const std::vector<qgi::WarmBatch> kernels =
+      qgi::warm_batches(qgi::setting_of(s.view), sv->max_batch, sv->ef_max, stop != nullptr);
+  size_t rows = 1;
+  for (const qgi::WarmBatch& b : kernels) rows = std::max(rows, (size_t)b.nq);
+  if (hipMemsetD32Async((hipDeviceptr_t)s.d_q, 0, D * rows, s.stream) != hipSuccess ||
+      hipMemsetD32Async((hipDeviceptr_t)s.d_k, 1, rows, s.stream) != hipSuccess ||
+      hipMemsetD32Async((hipDeviceptr_t)s.d_ef, 1, rows, s.stream) != hipSuccess)
+    return false;
+  for (const qgi::WarmBatch& b : kernels)
+    if (!search(b.nq, b.ef)) return false;
   std::memset(s.h_q, 0, sizeof(float) * D);
   s.h_k[0] = 1;
-  for (int64_t n : {65, 1}) {
-    if (n > sv->max_batch) continue;
-    for (int32_t ef : {1, 65, 129, 193, 257, 385, 513}) {
-      if (ef > sv->ef_max) break;
-      s.h_ef[0] = ef;
-      const bool in =
-          n == 1 ? hipMemcpyAsync(s.d_q, s.h_q, sizeof(float) * D, hipMemcpyHostToDevice, s.stream) == hipSuccess &&
-                       hipMemcpyAsync(s.d_k, s.h_k, sizeof(int32_t), hipMemcpyHostToDevice, s.stream) == hipSuccess &&
-                       hipMemcpyAsync(s.d_ef, s.h_ef, sizeof(int32_t), hipMemcpyHostToDevice, s.stream) == hipSuccess
-                 : hipMemsetD32Async((hipDeviceptr_t)s.d_q, 0, D * (size_t)n, s.stream) == hipSuccess &&
-                       hipMemsetD32Async((hipDeviceptr_t)s.d_k, 1, (size_t)n, s.stream) == hipSuccess &&
-                       hipMemsetD32Async((hipDeviceptr_t)s.d_ef, ef, (size_t)n, s.stream) == hipSuccess;
-      const bool ok =
-          in &&
-          (stop ? qg_search_mixed_stop(s.view, s.d_q, n, s.d_k, s.d_ef, sv->k_max, ef, 0, stop, s.d_ids, s.d_dists,
-                                       nullptr)
-                : qg_search_mixed(s.view, s.d_q, n, s.d_k, s.d_ef, sv->k_max, ef, 0, s.d_ids, s.d_dists, nullptr)) ==
-              QG_OK &&
-          hipMemcpyAsync(s.h_ids, s.d_ids, sizeof(int32_t) * K, hipMemcpyDeviceToHost, s.stream) == hipSuccess &&
-          hipMemcpyAsync(s.h_dists, s.d_dists, sizeof(float) * K, hipMemcpyDeviceToHost, s.stream) == hipSuccess &&
-          hipEventRecord(s.done, s.stream) == hipSuccess && hipEventSynchronize(s.done) == hipSuccess &&
-          hipEventQuery(s.done) == hipSuccess;
-      if (!ok) return false;
-    }
+  for (int32_t ef : {1, 65, 129}) {
+    if (ef > sv->ef_max) break;
+    s.h_ef[0] = ef;
+    const bool ok =
+        hipMemcpyAsync(s.d_q, s.h_q, sizeof(float) * D, hipMemcpyHostToDevice, s.stream) == hipSuccess &&
+        hipMemcpyAsync(s.d_k, s.h_k, sizeof(int32_t), hipMemcpyHostToDevice, s.stream) == hipSuccess &&
+        hipMemcpyAsync(s.d_ef, s.h_ef, sizeof(int32_t), hipMemcpyHostToDevice, s.stream) == hipSuccess &&
+        search(1, ef) &&
+        hipMemcpyAsync(s.h_ids, s.d_ids, sizeof(int32_t) * K, hipMemcpyDeviceToHost, s.stream) == hipSuccess &&
+        hipMemcpyAsync(s.h_dists, s.d_dists, sizeof(float) * K, hipMemcpyDeviceToHost, s.stream) == hipSuccess &&
+        hipEventRecord(s.done, s.stream) == hipSuccess && hipEventSynchronize(s.done) == hipSuccess &&
+        hipEventQuery(s.done) == hipSuccess;
+    if (!ok) return false;
   }
   return true;
 }
