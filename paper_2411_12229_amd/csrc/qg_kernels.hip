@@ -641,11 +641,11 @@ struct BlockView {
   static constexpr int BPL = CB / LPN;      // code bytes per lane
   static constexpr int DPL = (D + 63) / 64; // raw dims per lane
   static constexpr bool PLANES = qgl::use_planes(D, R);
-  static constexpr bool WORDS = PLANES || (BPL % 4) == 0;
-  // 32- or 16-bit code units per lane; with bit planes the D / 32 words of a
-  // code are split over its lanes, rounded up (a lane past the end repeats the
-  // last word against empty planes)
-  static constexpr int NW = PLANES ? (D / 32 + LPN - 1) / LPN : WORDS ? BPL / 4 : BPL / 2;
+  // code words per lane; with bit planes the D / 32 words of a code are split
+  // over its lanes, rounded up (a lane past the end repeats the last word against
+  // empty planes)
+  static constexpr int NW = PLANES ? (D / 32 + LPN - 1) / LPN : BPL / 4;
+  static_assert(PLANES || (BPL % 4 == 0 && NW <= 4), "the table's shape has a few whole words a lane");
   // Whether a second block (the next vertex, prefetched) is held in registers
   // beside this one (every shape built here: at most 45 words per lane);
   // wider shapes would load the block when it is used instead.
@@ -670,12 +670,9 @@ struct BlockView {
         const int i = h * NW + w;
         cw[w] = reinterpret_cast<const uint32_t*>(cp)[LPN * NW == D / 32 || i < D / 32 ? i : D / 32 - 1];
       }
-    } else if constexpr (WORDS) {
-#pragma unroll
-      for (int w = 0; w < NW; ++w) cw[w] = reinterpret_cast<const uint32_t*>(cp)[w];
     } else {
 #pragma unroll
-      for (int w = 0; w < NW; ++w) cw[w] = reinterpret_cast<const uint16_t*>(cp)[w];
+      for (int w = 0; w < NW; ++w) cw[w] = reinterpret_cast<const uint32_t*>(cp)[w];
     }
     fa = reinterpret_cast<const float*>(blk + qgl::off_fadd(D, R))[j];
     fr = reinterpret_cast<const float*>(blk + qgl::off_fres(D, R))[j];
@@ -736,9 +733,9 @@ struct BlockView {
 #pragma unroll
     for (int s = 0; s < (NW + G - 1) / G; ++s) {
       if (G * (s + 1) < NW) fetch(s + 1, buf[(s + 1) & 1]);
-      // wide codes: no further planes are read before this step's are counted
-      // (the memory clobber holds the reads, the first count the order)
-      if constexpr (NW > 4) asm volatile("" : "+v"(acc[0])::"memory");
+      // no further planes are read before this step's are counted (the memory
+      // clobber holds the reads, the first count the order)
+      asm volatile("" : "+v"(acc[0])::"memory");
 #pragma unroll
       for (int i = 0; i < G; ++i)
         if (G * s + i < NW) {
@@ -752,13 +749,11 @@ struct BlockView {
           acc[1] = bcnt(c & b.z, acc[1]);
           acc[0] = bcnt(c & b.w, acc[0]);
         }
-      if constexpr (NW > 4) {
-        asm volatile(""
-                     : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5]), "+v"(acc[6])
-                     :
-                     : "memory");
-        __builtin_amdgcn_sched_barrier(0);
-      }
+      asm volatile(""
+                   : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5]), "+v"(acc[6])
+                   :
+                   : "memory");
+      __builtin_amdgcn_sched_barrier(0);
     }
     int s = acc[6];
 #pragma unroll
@@ -773,7 +768,7 @@ struct BlockView {
   __device__ __forceinline__ int fastscan(const void* lut, int lane, int pad, int qsum) const {
     if constexpr (PLANES) return popscan(static_cast<const uint4*>(lut), lane, qsum);
     constexpr int RPG = D / 4 / LPN;
-    constexpr int UNIT_NIB = WORDS ? 8 : 4;
+    constexpr int UNIT_NIB = 8;
     const int h = lane % LPN;
     // group h starts after h padding rows (pad = 1)
     const uint32_t b8 = lds_addr(static_cast<const int16_t*>(lut)) + (uint32_t)((h * RPG + pad * h) * 16 * LB);
@@ -785,14 +780,6 @@ struct BlockView {
       const uint32_t ev = LB == 4 ? (cw[w] << 2) & 0x3C3C3C3Cu : (cw[w] << 1) & 0x1E1E1E1Eu;
       const uint32_t od = LB == 4 ? (cw[w] >> 2) & 0x3C3C3C3Cu : (cw[w] >> 3) & 0x1E1E1E1Eu;
       s += lut_sum<0, UNIT_NIB, LB>(b8 + w * UNIT_NIB * 16 * LB, ev, od);
-      // wide codes: keep the lookups of one unit together, so that not all of
-      // them are in flight (and in registers) at once
-      if constexpr (NW > 4) {
-        // the running sum passes through here: this unit's lookups are summed
-        // (and their registers free) before the next unit's are issued
-        asm volatile("" : "+v"(s)::"memory");
-        __builtin_amdgcn_sched_barrier(0);
-      }
     }
     if constexpr (LPN == 2) s += xor_lane_i<1>(s);
     return s;
@@ -1594,8 +1581,8 @@ __device__ bool search_one(const SearchArgs& a, int64_t q, uint8_t* lds, const q
 }
 
 // Algorithm 1 with the beam in registers (ef up to 64 NB): lane i holds beam
-// entries i and 64 + i, each with a checked flag and a consumed-duplicate flag
-// (its vertex was expanded through another entry).  The loop is
+// entries i, 64 + i, ... (one a register), each with a checked flag and a
+// consumed-duplicate flag (its vertex was expanded through another entry).  The loop is
 // software-pipelined.  The next vertex to expand is known before the merge:
 // it is the smaller of the best new candidate and the first old entry neither
 // checked nor consumed.  Its block is prefetched, and at the top of the next
@@ -2161,10 +2148,11 @@ struct OccupancyOp {
 };
 
 // The kernel instantiation for (D, R), pass, mode, beam storage and LUT
-// entry width.  Register beams (nb 1, 2) exist for the main pass of the
-// plain, stop-only and mixed modes; the traced, "w/o ME" and overflow-pass
-// kernels keep the beam in LDS.  The int32 LUT (lb 4) exists for the main
-// pass of the plain and mixed modes (the ones the autotuner times).
+// entry width.  Register beams (nb 1 .. 4, 6, 8) exist for the main pass of the
+// plain, mixed and stop modes and for the inline pass, which the plain and mixed
+// modes have; the traced, "w/o ME" and overflow-pass kernels keep the beam in
+// LDS.  The int32 LUT (lb 4) exists for the main pass of the plain and mixed
+// modes where the shape has a table.
 template <int D, int R, class Op, class Ret>
 static Ret dispatch_mode(SearchPass pass, int ls, int nb, int lb, const Op& op, Ret bad) {
   const bool gv = pass == kOverflowPass;

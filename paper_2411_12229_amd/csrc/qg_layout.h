@@ -32,9 +32,10 @@ __host__ __device__ constexpr int align16(int x) { return (x + 15) & ~15; }
 // Wide vectors keep the raw query in LDS instead of registers.
 __host__ __device__ constexpr bool query_in_lds(int D) { return D > 256; }
 
-// Where the query's FastScan data is a table (use_planes): LUT rows are 16 int16 entries (32 bytes).  With two lanes per neighbour the
-// second lane's rows start one padding row later so that the two halves of a
-// wavefront read different LDS banks.
+// Where the query's FastScan data is a table (not use_planes), LUT rows are 16
+// int16 entries (32 bytes).  With two lanes per neighbour the second lane's rows
+// start one padding row later so that the two halves of a wavefront read
+// different LDS banks.
 __host__ __device__ constexpr int lut_rows_padded(int D, int R) { return D / 4 + (64 / R) - 1; }
 
 // Whether a shape sums codes against the query's bit planes instead of a table:
