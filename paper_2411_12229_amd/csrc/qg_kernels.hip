@@ -2020,8 +2020,10 @@ __device__ bool search_one_rb(const SearchArgs& a, int64_t q, uint8_t* lds, cons
 // registers 4-40 spilled values and gains a third wavefront: 960 x 64 at 3,000
 // queries, ef 48 440 against 385 us, ef 192 1,056 against 865 us, at 10,000
 // 1,148 against 1,079 us; 960 x 32, ef 300, 10,000 queries 4,275 against 3,362
-// us; nothing lost at 1,000.  Not for six registers at 960 x 64 (848 against
-// 1,029 us at 1,000 queries), nor with the stop, whose LDS sets the residency.
+// us; nothing lost at 1,000.  Not for six registers at 960 x 64 (ef 300, k
+// 100: 1,000 queries 955 against 1,258 us, 2,000 1,060 against 1,466, 3,000 1,758
+// against 1,693, 10,000 4,600 against 5,230), nor with the stop, whose LDS sets the
+// residency.
 // Measured not to pay: 4 for D = 768, R = 32 (4% faster at 10,000 queries, 2-4%
 // slower at 3,000 and 5,000).
 template <int D, int R, int LS, int NB, bool INL>
