@@ -26,6 +26,7 @@
 #include <cstring>
 #include <deque>
 #include <mutex>
+#include <new>
 #include <string>
 #include <thread>
 #include <vector>
@@ -169,8 +170,12 @@ bool warm_up(qg_server* sv, Slot& s, const qg_stop_params* stop) {
                  : qg_search_mixed(s.view, s.d_q, n, s.d_k, s.d_ef, sv->k_max, ef, 0, s.d_ids, s.d_dists, nullptr)) ==
            QG_OK;
   };
-  const std::vector<qgi::WarmBatch> kernels =
-      qgi::warm_batches(qgi::setting_of(s.view), sv->max_batch, sv->ef_max, stop != nullptr);
+  std::vector<qgi::WarmBatch> kernels;
+  try {
+    kernels = qgi::warm_batches(qgi::setting_of(s.view), sv->max_batch, sv->ef_max, stop != nullptr);
+  } catch (const std::bad_alloc&) {
+    return false;
+  }
   size_t rows = 1;
   for (const qgi::WarmBatch& b : kernels) rows = std::max(rows, (size_t)b.nq);
   if (hipMemsetD32Async((hipDeviceptr_t)s.d_q, 0, D * rows, s.stream) != hipSuccess ||
